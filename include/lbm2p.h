@@ -212,8 +212,9 @@ int lbm_moments_device(lbm_domain *d, double *rho, double *ux, double *uy);
 int lbm_moments_device_noalloc(lbm_domain *d, double *rho, double *ux, double *uy);
 
 /* Total mass M(t) = sum over fluid nodes of sum_a f*_a (FP64, summed in a
- * fixed order, so equal states give equal bits): the m of Sec. 3.2, whose
- * ratio m/m0 the paper plots in Figs. 4-8.  The post-collision
+ * way that no order rounds, so equal states give equal bits whatever the
+ * launch shape): the m of Sec. 3.2, whose ratio m/m0 the paper plots in
+ * Figs. 4-8.  The post-collision
  * populations carry the same mass as the pre-collision ones. */
 int lbm_total_mass(lbm_domain *d, double *out);
 
@@ -269,7 +270,9 @@ int lbm_negative_rest(lbm_domain *d, int64_t *count);
  * periodic domains, every rule but Zhao-Yong and the quadratic
  * interpolation, and link tables of fewer than 2^23 - 1 slots (LBM_EINVAL
  * otherwise);
- * the default is 1.  tile_h is the two-step kernel's rows per workgroup
+ * the default is 1.  (Under either setting a run may keep more steps on
+ * chip where that is faster; a tile_h given here always takes the two-step
+ * kernel.)  tile_h is the two-step kernel's rows per workgroup
  * (0 = default 16, at least 4).  An odd step count ends with a
  * single step.  After a two-step pass the moments and the wall force of
  * the last step come from a replay of the intermediate step, in buffers

@@ -16,7 +16,9 @@ UNITS = [("lbm2p.hip", ["-ffp-contract=off"]),
          ("batch.hip", ["-ffp-contract=off"]),
          ("noalloc.hip", ["-ffp-contract=off"]),
          ("launch_f64.hip", ["-ffp-contract=off"]),
-         ("launch_f32.hip", ["-ffp-contract=off"])]
+         ("launch_f32.hip", ["-ffp-contract=off"]),
+         ("launch_block_f64.hip", ["-ffp-contract=off"]),
+         ("launch_block_f32.hip", ["-ffp-contract=off"])]
 DEPS = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [
     os.path.join(ROOT, "include", "lbm2p.h")]
 LIB = os.path.join(HERE, "liblbm2p.so")

@@ -175,9 +175,10 @@ BInst make_inst(lbm_domain* d) {
     I.side_f_bytes = (unsigned)(9 * (d->save_f ? std::max(d->nslots, 1) : 1) * 8);
     I.side_idx = d->side_idx;
     I.psiw = d->psiw;
-    I.side_mom = d->side_mom;
+    I.side_mom = d->side_mom[0];  // (an instance's two are one)
     I.side_f = d->side_f;
     I.partial = d->partial;
+    I.mass = d->mass;
     I.nx = d->nx;
     I.ny = d->ny;
     I.pitch = d->pitch;
@@ -264,7 +265,7 @@ BatchLaunch launch_of(lbm_batch* b) {
     L.args.lblk = b->d_lblk;
     L.args.nlblk = b->d_nlblk;
     L.args.ninst = (int)b->inst.size();
-    L.args.tile_h = b->tile_h;
+    L.args.tile_h = seg_rows(b->tile_h);
     L.args.persistent = b->persistent;
     L.eos = b->bd.eos;
     L.storage = b->bd.storage;
@@ -608,7 +609,7 @@ int lbm_batch_info(lbm_batch* b, int64_t out[8]) {
         if (!d) continue;
         ++n;
         const int sc = strip_cols(b->tile_w);
-        tiles += ((d->nx + sc - 1) / sc) * (long long)((d->ny + b->tile_h - 1) / b->tile_h);
+        tiles += ((d->nx + sc - 1) / sc) * (long long)seg_count(d->ny, b->tile_h);
         lblk += (d->nslot_links + 255) / 256;
     }
     out[0] = n;

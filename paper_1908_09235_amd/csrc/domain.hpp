@@ -36,6 +36,25 @@ class Arena {
 
 }  // namespace lbm
 
+namespace lbm {
+
+// How a domain's runs of steps are cut into launches of k_block (steps per
+// launch; 0: not used), with the tables of its tiles on the device.
+struct BlockPlan {
+    int steps = 0, halo = 0, pull = 0;
+    int nstrips = 0, nsegs = 0, ntiles = 0, max_nodes = 0, max_len = 0;
+    unsigned link_bytes = 0, node_bytes = 0;
+    bool moving = false;
+    bool wide = false;   // 1024 lanes per tile
+    BlockTile* tiles = nullptr;
+    BlockLink* links = nullptr;
+    BlockNode* nodes = nullptr;
+    MassPart* partial[2] = {nullptr, nullptr};  // [step][tile], used in turn
+    int set = 0;                                // the one written last
+};
+
+}  // namespace lbm
+
 struct lbm_domain {
     int nx = 0, ny = 0, pitch = 0;
     long long plane = 0;
@@ -49,11 +68,13 @@ struct lbm_domain {
     uint8_t* flags = nullptr;
     float* psiw = nullptr;  // FP16 storage: psi_w of solid nodes in FP32
     int* side_idx = nullptr;
-    double* side_mom = nullptr;
+    double* side_mom[2] = {nullptr, nullptr};  // moments of the time of f[0], f[1]
     double* side_f = nullptr;
     int nslots = 0;
     bool save_f = false;
-    double* partial = nullptr;
+    // mass partials of the last pass: one array of partial_cap per step
+    lbm::MassPart* partial = nullptr;
+    lbm::MassUnit mass{};
     double* hist = nullptr;
     long long* unstable = nullptr;
     double* mom_out = nullptr;
@@ -75,12 +96,14 @@ struct lbm_domain {
     // is its own pass); eligible when the form allows it.
     int fused = 1;
     bool fusable = false;
+    bool tile_h2_asked = false;  // by the caller, not the default
     int tile_h2 = 0, nstrips2 = 0, nsegs2 = 0, nblocks2 = 0;
     int* node_link = nullptr;    // per node (pitch layout): first link slot + 1, or 0
     int* tile_order = nullptr;   // tile of each workgroup of the two-step pass
     std::vector<int> bnd_x, bnd_y;  // host: the boundary nodes (tile weights)
-    double* partial2 = nullptr;  // masses of the second step of a pass
     int pending_steps = 0;       // steps of the last pass whose masses are pending
+    bool pending_block = false;  // it was a launch of k_block
+    lbm::BlockPlan block;
     // After a two-step pass f*(t - 1) is not in memory: the buffer that
     // held f*(t - 2) still does, with the ghosts of step t - 1, and the
     // moments at t and the wall force of the last step are read from a

@@ -45,8 +45,8 @@ struct Main2Args {
     const int* __restrict__ order;        // tile of each workgroup (null: XCD order)
     const float* __restrict__ psiw;       // FP16 storage: psi_w of solid nodes
     double* __restrict__ side_mom;        // moments of t + 2 of flagged nodes
-    double* __restrict__ partial1;        // per workgroup: mass at t + 1
-    double* __restrict__ partial2;        // per workgroup: mass at t + 2
+    MassPart* __restrict__ partial1;      // per workgroup: mass at t + 1
+    MassPart* __restrict__ partial2;      // per workgroup: mass at t + 2
     const int* __restrict__ lmeta;        // link tables (see BndArgs)
     const double* __restrict__ lc;
     const double* __restrict__ luw;
@@ -57,6 +57,7 @@ struct Main2Args {
     long long plane;
     int tile_h, nsegs, nstrips;
     unsigned side_mom_bytes;
+    MassUnit mass;
 };
 
 template <typename S>
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
         ps[8] = ring[km][cr];
     };
 
-    double msum1 = 0.0, msum2 = 0.0;
+    MassSum<sizeof(R) == 8 || DEV != 0> msum1, msum2;
     Pull2<S> fcur{}, fnxt{};      // pulled f(t + 2) of rows k - 2 and k - 1
 
     // the wall rules of step t + 2 for the boundary node of lane j in row m
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
         const int slot = r1(m);
         auto fst = [&](int q, int row, int l) {
             const double v = double(fs1[r1(row)][q][lane(l)]);
-            return DEV == 1 ? v + wt(q) * double(ph.rref) : v;
+            return DEV == 1 ? v + lane_wt(q) * double(ph.rref) : v;
         };
         const double m0 = double(mo1[rm(m)][0][j]);
         const double rho_b = DEV == 1 ? double(ph.rref) + m0 : m0;
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
 #pragma unroll
             for (int q = 0; q < 7; ++q) c[q] = a.lc[8 * i + q];
             const double uwx = a.luw[2 * i], uwy = a.luw[2 * i + 1];
-            const int od = opp(d), dx = cx(d), dy = cy(d);
+            const int od = lane_opp(d), dx = lane_cx(d), dy = lane_cy(d);
             fab = fst(d, m, j);
             return link_value(kind, d, c, uwx, uwy, fab, rho_b, ubx, uby, ch, bk, wl,
                               [&](int what) -> double {
@@ -267,8 +268,8 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
             out_sum += fab;
             in_sum += r + wl;
             // the incoming population, as the ghost slot would hold it
-            const S g = S(r - (DEV == 1 ? wt(d) * double(ph.rref) : 0.0));
-            const int od = opp(d);
+            const S g = S(r - (DEV == 1 ? lane_wt(d) * double(ph.rref) : 0.0));
+            const int od = lane_opp(d);
 #pragma unroll
             for (int q = 1; q < 9; ++q)
                 if (q == od) f.f[q] = g;
@@ -301,7 +302,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
             R rho, drho, ux, uy, Fx, Fy;
             node_moments<R, EOS, DEV>(fc, ps, ph, rho, drho, ux, uy, Fx, Fy);
             const double rho_d = DEV == 1 ? double(ph.rref) + double(drho) : double(rho);
-            msum1 += (fluid && outc && k >= 3 && k < H + 3) ? rho_d : 0.0;
+            msum1.add(fluid && outc && k >= 3 && k < H + 3, rho_d, a.mass);
             R dh[9];
             collide<R>(fc, rho, drho, ux, uy, Fx, Fy, ph, dh);
             const int s = r1(k);
@@ -342,7 +343,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
             R rho, drho, ux, uy, Fx, Fy;
             node_moments<R, EOS, DEV>(fc, ps, ph, rho, drho, ux, uy, Fx, Fy);
             const double rho_d = DEV == 1 ? double(ph.rref) + double(drho) : double(rho);
-            msum2 += live ? rho_d : 0.0;
+            msum2.add(live, rho_d, a.mass);
             const bool sm = live && (nf & FL_SAVE_MOM);
             if (__builtin_amdgcn_ballot_w64(sm)) {
                 const unsigned so = sm ? (unsigned)msi[rm(n)][j] * 24u : kOOB;
@@ -377,12 +378,8 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
         step(k + 2, C, A);
     }
 
-    // fixed-order wavefront reductions of the two mass partials
-    double v1 = msum1, v2 = msum2;
-    for (int off = 32; off > 0; off >>= 1) {
-        v1 += __shfl_down(v1, off, 64);
-        v2 += __shfl_down(v2, off, 64);
-    }
+    const MassPart v1 = mass_wave_sum(mass_part(msum1.a, msum1.b, a.mass.inv));
+    const MassPart v2 = mass_wave_sum(mass_part(msum2.a, msum2.b, a.mass.inv));
     if (j == 0) {
         a.partial1[tile] = v1;
         a.partial2[tile] = v2;

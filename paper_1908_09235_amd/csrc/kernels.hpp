@@ -23,8 +23,8 @@
 //     also pulls the strip's two halo columns.  Solid nodes are not
 //     stored.  Boundary nodes (and the x_f nodes that MLS reads) save their
 //     moments, and under Zhao-Yong their pre-collision populations, for the
-//     next k_boundary.  Each workgroup writes one FP64 partial of the total
-//     mass; the next launch reduces the partials in a fixed order.
+//     next k_boundary.  Each workgroup writes one exact partial of the total
+//     mass (MassPart); the next launch adds the partials.
 #pragma once
 
 #include "lattice.hpp"
@@ -46,6 +46,90 @@ __host__ __device__ __forceinline__ int xcd_tile(int b, int nb) {
     return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
 }
 
+// Total mass.  The FP64 density of every fluid node is split, exactly, into a
+// multiple of `unit` (2^-40 of the largest initial density, or a little more)
+// and the rest, and both are added in FP64.  Sums of such multiples below
+// 2^53 units are exact (128 times the initial density and more, at every
+// place here), and so are those of the rests, whatever the order; the sums of
+// lanes, tiles and workgroups go on as integers.  So a step's mass is rounded
+// once, at the end, and has the same bits for every tile shape, for one or
+// several steps per launch, alone or in a batch.  In a run that breaks down
+// the sums round as FP64 sums do, and become non-finite with the densities.
+struct MassUnit {
+    double magic;  // 1.5 * 2^52 units: (x + magic) - magic is x in whole units
+    double unit, inv;  // inv = 1 / unit, both powers of two
+};
+constexpr double kMassFine = 1.0 / 1099511627776.0;
+struct MassPart {
+    long long lo, hi;  // units: lo + 2^32 hi
+    long long fine;    // of 2^-40 units (kMassFine)
+    double big;        // what integers do not hold
+};
+// Rows one lane adds up at most: 2^51 units each, in 63 bits.  A tile of more
+// rows runs as several.
+constexpr int kMassRows = 2048;
+__host__ __device__ constexpr int seg_rows(int tile_h) {
+    return tile_h < kMassRows ? tile_h : kMassRows;
+}
+__host__ __device__ constexpr int seg_count(int ny, int tile_h) {
+    return (ny + seg_rows(tile_h) - 1) / seg_rows(tile_h);
+}
+
+// What one lane adds up.  SPLIT: as above.  An FP32 density is a multiple of
+// the unit as it is (down to 2^-16 of the largest).
+template <bool SPLIT>
+struct MassSum {
+    double a = 0.0, b = 0.0;
+    __device__ __forceinline__ void add(bool live, double rho, const MassUnit& m) {
+        const double r = live ? rho : 0.0;
+        if constexpr (SPLIT) {
+            const double x = (r + m.magic) - m.magic;
+            a += x;
+            b += r - x;
+        } else {
+            a += r;
+        }
+    }
+};
+
+// A sum of multiples and rests in integers.
+__device__ __forceinline__ MassPart mass_part(double a, double b, double inv) {
+    const double n = a * inv, r = b * inv;
+    if (!(fabs(n) < 9007199254740992.0 && fabs(r) <= 4194304.0))
+        return MassPart{0, 0, 0, a + b};
+    // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
+    const double w = rint(n);
+    const long long q = (long long)w;
+    const long long f = (long long)rint(((n - w) + r) * (1.0 / kMassFine));
+    return MassPart{q & 0xffffffffll, q >> 32, f, 0.0};
+}
+__device__ __forceinline__ void mass_take(MassPart& v, const MassPart& p) {
+    v.lo += p.lo;
+    v.hi += p.hi;
+    v.fine += p.fine;
+    v.big += p.big;
+}
+// Sum over the lanes of a wavefront, in lane 0.
+__device__ __forceinline__ MassPart mass_wave_sum(MassPart p) {
+    for (int off = 32; off > 0; off >>= 1) {
+        p.lo += __shfl_down(p.lo, off, 64);
+        p.hi += __shfl_down(p.hi, off, 64);
+        p.fine += __shfl_down(p.fine, off, 64);
+        p.big += __shfl_down(p.big, off, 64);
+    }
+    return p;
+}
+__device__ __forceinline__ double mass_value(MassPart p, double unit) {
+    // carries upwards, then three exact doubles, rounded as one sum: the
+    // lowest part decides only how the sum of the others rounds
+    const long long lo = p.lo + (p.fine >> 40);
+    const long long hi = p.hi + (lo >> 32);
+    const double l = double(lo & 0xffffffffll), f = double(p.fine & 0xffffffffffll);
+    const double h = double(hi) * 4294967296.0;
+    const double s = h + l, e = l - (s - h);  // h + l = s + e
+    return (s + fma(f, kMassFine, e)) * unit + p.big;
+}
+
 template <typename S>
 struct MainArgs {
     const S* __restrict__ src;
@@ -55,12 +139,13 @@ struct MainArgs {
     const float* __restrict__ psiw;     // FP16 storage: psi_w of solid nodes
     double* __restrict__ side_mom;      // [slot][3]: rho, ux, uy
     double* __restrict__ side_f;        // [slot][9]: pre-collision f
-    double* __restrict__ partial;       // per workgroup
+    MassPart* __restrict__ partial;     // per workgroup
     double* __restrict__ mom_out;       // moments mode: rho, ux, uy planes
     int nx, ny, pitch;
     long long plane;                    // elements per population plane
     int tile_h, nsegs, nstrips;
     unsigned side_mom_bytes, side_f_bytes;
+    MassUnit mass;
 };
 
 // Buffer resources: a 32-bit byte range on an SGPR base, so that a load
@@ -97,6 +182,16 @@ __device__ __forceinline__ _Float16 bload<_Float16>(rsrc_t r, unsigned v, unsign
 template <>
 __device__ __forceinline__ uint8_t bload<uint8_t>(rsrc_t r, unsigned v, unsigned s) {
     return __builtin_amdgcn_raw_buffer_load_b8(r, v, s, 0);
+}
+typedef __attribute__((ext_vector_type(4))) unsigned uint4_t;
+template <>
+__device__ __forceinline__ uint4_t bload<uint4_t>(rsrc_t r, unsigned v, unsigned s) {
+    return __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(r, v, s, 0));
+}
+typedef __attribute__((ext_vector_type(2))) unsigned uint2_t;
+template <>
+__device__ __forceinline__ uint2_t bload<uint2_t>(rsrc_t r, unsigned v, unsigned s) {
+    return __builtin_bit_cast(uint2_t, __builtin_amdgcn_raw_buffer_load_b64(r, v, s, 0));
 }
 __device__ __forceinline__ void bstore(float x, rsrc_t r, unsigned v, unsigned s) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, v, s, 0);
@@ -184,7 +279,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
     // computed (the FP16 per-node form's density ring assumes three)
     static_assert(RING >= 2 && RING <= 4 && (DEV != 2 || RING == 3), "unsupported ring");
     __shared__ R ring[4][kMaxTileW];
-    __shared__ double wsum[kMaxTileW / 64];
+    __shared__ MassPart wsum[kMaxTileW / 64];
     constexpr unsigned ES = sizeof(S);
     // DEV 2: the density plane's rows -2 .. H + 1 of the strip, with one
     // column more on either side, pass through an LDS ring of eight rows:
@@ -334,7 +429,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
         ring[slot][tid] = (L.fl & FL_SOLID) ? pw : psi_of<EOS, R>(rho, ph);
     };
 
-    double msum = 0.0;
+    MassSum<sizeof(R) == 8 || DEV != 0> msum;
     // row k: collide with psi of rows k-1, k, k+1; then prefetch row k+3
     auto step = [&](int k, RowLoad<S, R, NR>& Lc, RowLoad<S, R, NR>& Ln) {
         const int y = row_of(k);
@@ -372,7 +467,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
 #pragma unroll
                 for (int q = 0; q < 9; ++q) rho_d += fma(wt(q), double(rr[q]), double(Lc.f[q]));
             }
-            msum += live ? rho_d : 0.0;
+            msum.add(live, rho_d, a.mass);
             // moments of boundary nodes (and pre-collision populations)
             // (stores only from a wavefront with such a node in the row:
             // the branch is uniform, and the waits for the rows in flight
@@ -443,14 +538,12 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
     }
 
     if constexpr (!MOMENTS) {
-        // fixed-order block reduction of the mass partial
-        double v = msum;
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+        const MassPart v = mass_wave_sum(mass_part(msum.a, msum.b, a.mass.inv));
         if ((tid & 63) == 0) wsum[tid >> 6] = v;
         __syncthreads();
         if (tid == 0) {
-            double t = 0.0;
-            for (int w = 0; w < (W + 63) / 64; ++w) t += wsum[w];
+            MassPart t = wsum[0];
+            for (int w = 1; w < (W + 63) / 64; ++w) mass_take(t, wsum[w]);
             a.partial[tile] = t;
         }
     }
@@ -461,80 +554,80 @@ __global__ __launch_bounds__(256) void k_main(MainArgs<S> a, Phys<R> ph) {
     main_tile<S, R, EOS, MOMENTS, DEV, SAVEF>(a, ph, xcd_tile(blockIdx.x, gridDim.x));
 }
 
-// Sum the main kernel's partials in a fixed order; the total lands in
-// thread 0.
-__device__ __forceinline__ double sum_partials(const double* __restrict__ partial, int np) {
-    __shared__ double red[256];
-    const int tid = threadIdx.x;
-    // each thread adds partials tid, tid + 256, ... in that order; eight
-    // loads are issued before their additions
-    double v = 0.0;
-    int i = tid;
-    for (; i + 7 * 256 < np; i += 8 * 256) {
-        double q[8];
+// The partials lane `lane` of `lanes` adds up.
+__device__ __forceinline__ MassPart sum_partials(const MassPart* __restrict__ partial, int np,
+                                                 int lane, int lanes) {
+    MassPart v{0, 0, 0, 0.0};
+    // four loads are issued before their additions
+    int i = lane;
+    for (; i + 3 * lanes < np; i += 4 * lanes) {
+        MassPart q[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) q[j] = partial[i + j * 256];
+        for (int j = 0; j < 4; ++j) q[j] = partial[i + j * lanes];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v += q[j];
+        for (int j = 0; j < 4; ++j) mass_take(v, q[j]);
     }
-    for (; i < np; i += 256) v += partial[i];
-    red[tid] = v;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
+    for (; i < np; i += lanes) mass_take(v, partial[i]);
+    return v;
+}
+
+constexpr int kReduceWaves = 16;  // of a workgroup that sums partials, at most
+
+// The masses of `steps` steps, whose np partials each lie `stride` apart, by
+// one workgroup: the wavefronts share the steps (all of them one step if
+// there is only one), and put(s, mass) runs in thread 0, in step order.
+template <typename F>
+__device__ __forceinline__ void sum_masses(const MassPart* __restrict__ partial, int np, int steps,
+                                           long long stride, double unit, F&& put) {
+    __shared__ MassPart red[kReduceWaves];
+    const int nw = (int)blockDim.x / 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int s0 = 0; s0 < steps; s0 += nw) {
+        const int cnt = min(nw, steps - s0), share = nw / cnt;  // wavefronts of a step
+        const int s = wave / share, part = wave - s * share;
+        if (s < cnt) {
+            const MassPart v = mass_wave_sum(sum_partials(partial + (s0 + s) * stride, np,
+                                                          part * 64 + lane, share * 64));
+            if (lane == 0) red[wave] = v;
+        }
         __syncthreads();
-    }
-    return red[0];
-}
-
-// The total into hist[slot], and the first non-finite one into unstable.
-__device__ __forceinline__ void reduce_partials(const double* __restrict__ partial,
-                                                int np, double* __restrict__ hist,
-                                                long long slot, long long t,
-                                                long long* __restrict__ unstable) {
-    const double m = sum_partials(partial, np);
-    if (threadIdx.x == 0) {
-        hist[slot] = m;
-        if (!isfinite(m) && *unstable < 0) *unstable = t;
+        if (threadIdx.x == 0)
+            for (int k = 0; k < cnt; ++k) {
+                MassPart v = red[k * share];
+                for (int w = 1; w < share; ++w) mass_take(v, red[k * share + w]);
+                put(s0 + k, mass_value(v, unit));
+            }
+        __syncthreads();  // red may be written again
     }
 }
 
-// As reduce_partials, with the step taken from a device clock that holds
-// the step of the last recorded mass and advances by one: the launches of
-// a step then need no argument that changes from step to step, so a
-// captured graph of steps can be replayed.
-__device__ __forceinline__ void reduce_on_clock(const double* __restrict__ partial, int np,
-                                                double* __restrict__ hist, long long cap,
-                                                long long* __restrict__ clock,
-                                                long long* __restrict__ unstable) {
-    const double m = sum_partials(partial, np);
-    if (threadIdx.x == 0) {
-        const long long t = *clock + 1;
-        hist[t % cap] = m;
-        if (!isfinite(m) && *unstable < 0) *unstable = t;
-        *clock = t;
-    }
-}
-
-// The masses of the last pass: one step (partial2 null) or two steps per
-// pass (partial, then partial2), each recorded at the next step of the clock.
-__device__ __forceinline__ void reduce_pass(const double* __restrict__ partial,
-                                            const double* __restrict__ partial2, int np,
-                                            double* __restrict__ hist, long long cap,
-                                            long long* __restrict__ clock,
-                                            long long* __restrict__ unstable) {
-    reduce_on_clock(partial, np, hist, cap, clock, unstable);
-    if (partial2) {
-        __syncthreads();  // every thread has read the first total
-        reduce_on_clock(partial2, np, hist, cap, clock, unstable);
-    }
+// The masses of the last pass: `steps` steps, whose partials lie in arrays
+// `stride` apart.  The step of each comes from a device clock that holds
+// the step of the last recorded mass and advances by one: the launches of a
+// step then need no argument that changes from step to step, so a captured
+// graph of steps can be replayed.
+struct MassPass {
+    const MassPart* __restrict__ partial;
+    int np, steps;
+    long long stride;
+    double unit;
+    double* __restrict__ hist;
+    long long cap;                   // history ring entries
+    long long* __restrict__ clock;   // step of the last recorded mass
+    long long* __restrict__ unstable;
+};
+__device__ __forceinline__ void reduce_pass(const MassPass& r) {
+    long long t = threadIdx.x == 0 ? *r.clock : 0;
+    sum_masses(r.partial, r.np, r.steps, r.stride, r.unit, [&](int, double m) {
+        ++t;
+        r.hist[t % r.cap] = m;
+        if (!isfinite(m) && *r.unstable < 0) *r.unstable = t;
+    });
+    if (threadIdx.x == 0) *r.clock = t;
 }
 
 template <int Unused = 0>
-__global__ __launch_bounds__(256) void k_reduce(const double* partial, const double* partial2,
-                                                int np, double* hist, long long cap,
-                                                long long* clock, long long* unstable) {
-    reduce_pass(partial, partial2, np, hist, cap, clock, unstable);
+__global__ __launch_bounds__(256) void k_reduce(MassPass r) {
+    reduce_pass(r);
 }
 
 // ---------------------------------------------------------------- boundary
@@ -573,15 +666,8 @@ struct BndArgs {
     const int* __restrict__ lref;    // DEV 2: side slot whose density encodes
                                      // the ghost (one boundary node per ghost)
     int fix;                         // 0 none, 1 A, 2 B, 3 Bao
-    // reduction of the previous main launch's mass partials (last block):
-    // one array per step of that launch (partial2 null for a single step)
-    const double* __restrict__ partial;
-    const double* __restrict__ partial2;
-    int np;
-    double* __restrict__ hist;
-    long long cap;                   // history ring entries
-    long long* __restrict__ clock;   // step of the last recorded mass
-    long long* __restrict__ unstable;
+    // reduction of the previous main launch's mass partials (last block)
+    MassPass prev;
     int do_reduce;
     // force on the walls (Sec. 4.2, momentum exchange): two FP64 partials
     // per link block (null: not formed)
@@ -619,9 +705,10 @@ __device__ __forceinline__ double link_value(int kind, int d, const double* c, d
                                              double uwy, double fab, double rho_b, double ubx,
                                              double uby, double& ch, double& bk, double& wl,
                                              F&& fetch) {
-    const double ex = double(cx(d)), ey = double(cy(d));
+    const int dx = lane_cx(d), dy = lane_cy(d);
+    const double ex = double(dx), ey = double(dy), w = lane_wt(d);
     // momentum of a moving wall, Ladd / Mei et al.: 2 w_a rho_b e.u_w / c_s^2
-    wl = 2.0 * wt(d) * rho_b * 3.0 * (ex * uwx + ey * uwy);
+    wl = 2.0 * w * rho_b * 3.0 * (ex * uwx + ey * uwy);
     ch = 0.0;
     bk = 0.0;
     if (kind == LK_HALFWAY) return fab - wl;
@@ -639,10 +726,10 @@ __device__ __forceinline__ double link_value(int kind, int d, const double* c, d
         }
         ch = c[3];
         // Eq. (8): w_a [1 + 3 e.u_s + 4.5 (e.u_b)^2 - 1.5 u_b^2]
-        const double eus = edot<double>(d, usx, usy);
-        const double eub = edot<double>(d, ubx, uby);
+        const double eus = lane_edot(dx, dy, usx, usy);
+        const double eub = lane_edot(dx, dy, ubx, uby);
         const double ub2 = ubx * ubx + uby * uby;
-        bk = wt(d) * (1.0 + 3.0 * eus + 4.5 * (eub * eub) - 1.5 * ub2);
+        bk = w * (1.0 + 3.0 * eus + 4.5 * (eub * eub) - 1.5 * ub2);
         return (1.0 - ch) * fab + ch * (rho_b * bk) - wl;  // Eq. (7)
     }
     if (kind == LK_LIN_F) return c[0] * fab + c[1] * fetch(LV_D_F);
@@ -669,8 +756,8 @@ __device__ __forceinline__ void boundary_block(S* __restrict__ A, const BndArgs&
     // DEV 2: densities of the nodes, after the nine population planes
     float* const rpl = reinterpret_cast<float*>(A + 9 * P);
     auto ld = [&](int q, int n) {
-        if constexpr (DEV == 2) return double(A[q * P + n]) + wt(q) * double(rpl[n]);
-        return DEV == 1 ? double(A[q * P + n]) + wt(q) * b.rref : double(A[q * P + n]);
+        if constexpr (DEV == 2) return double(A[q * P + n]) + lane_wt(q) * double(rpl[n]);
+        return DEV == 1 ? double(A[q * P + n]) + lane_wt(q) * b.rref : double(A[q * P + n]);
     };
     // the link's record, loaded beside its metadata (a padding slot of the
     // table stands in for the lanes past its end): one round trip fewer
@@ -690,7 +777,7 @@ __device__ __forceinline__ void boundary_block(S* __restrict__ A, const BndArgs&
     double fab = 0.0, r = 0.0, ch = 0.0, bk = 0.0, wl = 0.0;
     if (active) {
         node = node_r;
-        const int od = opp(d);
+        const int od = lane_opp(d);
         const double* mom = b.side_mom + 3 * slotb;
         fab = ld(d, node);
         r = link_value(kind, d, c, uwx, uwy, fab, mom[0], mom[1], mom[2], ch, bk, wl,
@@ -746,15 +833,15 @@ __device__ __forceinline__ void boundary_block(S* __restrict__ A, const BndArgs&
     }
     if (active) {
         const int g = ghost;
-        double enc = DEV == 1 ? wt(d) * b.rref : 0.0;
+        double enc = DEV == 1 ? lane_wt(d) * b.rref : 0.0;
         if constexpr (DEV == 2) {
             // every link into ghost g encodes against the same density: that
             // of one boundary node next to it, which one of them records
             const float rg = float(b.side_mom[3 * gref]);
             if ((meta >> 16) & 1) rpl[g] = rg;
-            enc = wt(d) * double(rg);
+            enc = lane_wt(d) * double(rg);
         }
-        A[opp(d) * P + g] = S(r - enc);
+        A[lane_opp(d) * P + g] = S(r - enc);
     }
     if (head && b.fix == 1) {
         // Eq. (15) without the wall momentum, added to the rest population
@@ -781,8 +868,8 @@ __device__ __forceinline__ void boundary_block(S* __restrict__ A, const BndArgs&
         // wavefront sums
         __shared__ double s_fx[4], s_fy[4];
         const double m = fab + r;
-        double vx = active ? double(cx(d)) * m : 0.0;
-        double vy = active ? double(cy(d)) * m : 0.0;
+        double vx = active ? double(lane_cx(d)) * m : 0.0;
+        double vy = active ? double(lane_cy(d)) * m : 0.0;
         for (int off = 32; off > 0; off >>= 1) {
             vx += __shfl_down(vx, off, 64);
             vy += __shfl_down(vy, off, 64);
@@ -845,7 +932,7 @@ __device__ __forceinline__ void open_rows(S* __restrict__ A, const BndArgs& b, i
 template <typename S, int DEV>
 __global__ __launch_bounds__(256) void k_boundary(S* __restrict__ A, BndArgs b) {
     if (blockIdx.x == gridDim.x - 1) {
-        if (b.do_reduce) reduce_pass(b.partial, b.partial2, b.np, b.hist, b.cap, b.clock, b.unstable);
+        if (b.do_reduce) reduce_pass(b.prev);
         return;
     }
     if (int(blockIdx.x) >= b.nlink_blocks) {
@@ -918,7 +1005,8 @@ struct BInst {
     const float* psiw;
     double* side_mom;
     double* side_f;
-    double* partial;  // one FP64 mass partial per tile
+    MassPart* partial;  // one mass partial per tile
+    MassUnit mass;
     int nx, ny, pitch, nsegs, nstrips, np;
     unsigned side_mom_bytes, side_f_bytes;
     long long plane;
@@ -960,25 +1048,6 @@ struct BatchArgs {
     int persistent;                  // 1: tile queues, 0: one workgroup per tile
 };
 
-// Tables that a launch only reads (the instance descriptors, states, tile
-// and link-block lists: written by the host, or by earlier launches), read
-// through the constant address space.  The compiler then loads them from a
-// uniform address with scalar loads into scalar registers, as it does the
-// kernel arguments; read through a generic pointer they come in as vector
-// loads (the launch's own stores might alias them) and every use needs a
-// v_readfirstlane.  The scalar cache is invalidated when a launch starts.
-// (The host pass of the compiler, which only checks these functions, has no
-// such address space.)
-#if defined(__HIP_DEVICE_COMPILE__)
-#define LBM_CONST_AS __attribute__((address_space(4)))
-#else
-#define LBM_CONST_AS
-#endif
-template <typename T>
-__device__ __forceinline__ const LBM_CONST_AS T* ro(const T* p) {
-    return (const LBM_CONST_AS T*)p;
-}
-
 template <typename S, typename I_t>
 __device__ __forceinline__ MainArgs<S> inst_main_args(const I_t& I, long long t, int tile_h) {
     MainArgs<S> a;
@@ -991,6 +1060,9 @@ __device__ __forceinline__ MainArgs<S> inst_main_args(const I_t& I, long long t,
     a.side_mom = I.side_mom;
     a.side_f = I.side_f;
     a.partial = I.partial;
+    a.mass.magic = I.mass.magic;
+    a.mass.unit = I.mass.unit;
+    a.mass.inv = I.mass.inv;
     a.mom_out = nullptr;
     a.nx = I.nx;
     a.ny = I.ny;
@@ -1080,13 +1152,6 @@ __global__ __launch_bounds__(256) void k_boundary_batch(BatchArgs b) {
         a.rref = I.rref;
         a.lref = I.lref;
         a.fix = I.fix;
-        a.partial = nullptr;
-        a.partial2 = nullptr;
-        a.np = 0;
-        a.hist = nullptr;
-        a.cap = 1;
-        a.clock = nullptr;
-        a.unstable = nullptr;
         a.do_reduce = 0;
         a.force = nullptr;
         a.negrest = nullptr;
@@ -1100,7 +1165,7 @@ __global__ __launch_bounds__(256) void k_boundary_batch(BatchArgs b) {
     }
 }
 
-// Per instance: M(t+1) from the main pass's partials in a fixed order, the
+// Per instance: M(t+1) from the main pass's partials, the
 // first non-finite mass, t += 1 and one step fewer to run (none once
 // unstable).  Also empties the tile queues for the next main pass.
 template <int Unused = 0>
@@ -1112,7 +1177,10 @@ __global__ __launch_bounds__(256) void k_reduce_batch(BatchArgs b) {
         const auto& I = ro(b.inst)[i];
         const long long t1 = st->t + 1;
         __syncthreads();
-        reduce_partials(I.partial, I.np, I.hist, t1 % I.cap, t1, I.unstable);
+        sum_masses(I.partial, I.np, 1, 0, I.mass.unit, [&](int, double m) {
+            I.hist[t1 % I.cap] = m;
+            if (!isfinite(m) && *I.unstable < 0) *I.unstable = t1;
+        });
         if (threadIdx.x == 0) {
             st->t = t1;
             st->remaining = *I.unstable >= 0 ? 0 : rem - 1;

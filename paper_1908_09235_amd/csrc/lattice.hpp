@@ -43,6 +43,42 @@ __host__ __device__ __forceinline__ R edot(int a, R vx, R vy) {
     }
 }
 
+// The same for a direction that differs from lane to lane, from packed tables
+// (the conditions above would run as branches one after another).
+namespace packed {
+constexpr unsigned pack_e(int k) {
+    unsigned v = 0;
+    for (int a = 0; a < 9; ++a) v |= (unsigned)((k ? cy(a) : cx(a)) + 1) << (2 * a);
+    return v;
+}
+constexpr unsigned long long pack_opp() {
+    unsigned long long v = 0;
+    for (int a = 0; a < 9; ++a) v |= (unsigned long long)opp(a) << (4 * a);
+    return v;
+}
+constexpr unsigned kEx = pack_e(0), kEy = pack_e(1);
+constexpr unsigned long long kOpp = pack_opp();
+}  // namespace packed
+__host__ __device__ __forceinline__ int lane_cx(int a) {
+    return (int)((packed::kEx >> (2 * a)) & 3u) - 1;
+}
+__host__ __device__ __forceinline__ int lane_cy(int a) {
+    return (int)((packed::kEy >> (2 * a)) & 3u) - 1;
+}
+__host__ __device__ __forceinline__ int lane_opp(int a) {
+    return (int)((packed::kOpp >> (4 * a)) & 15u);
+}
+__host__ __device__ __forceinline__ double lane_wt(int a) {  // a >= 1
+    return a <= 4 ? wt(1) : wt(5);
+}
+// e_a . v: the sum of the selected components; equal to edot but for the sign
+// of a zero.
+__host__ __device__ __forceinline__ double lane_edot(int ex, int ey, double vx, double vy) {
+    const double tx = ex == 0 ? 0.0 : (ex < 0 ? -vx : vx);
+    const double ty = ey == 0 ? 0.0 : (ey < 0 ? -vy : vy);
+    return tx + ty;
+}
+
 // physical parameters, in the compute type
 template <typename R>
 struct Phys {
@@ -184,6 +220,25 @@ __device__ __forceinline__ void collide(const R f[9], R rho, R drho, R ux, R uy,
     dh[6] = g6;
     dh[7] = g7;
     dh[8] = g8;
+}
+
+// Tables that a launch only reads (the instance descriptors, states, tile
+// and link-block lists: written by the host, or by earlier launches), read
+// through the constant address space.  The compiler then loads them from a
+// uniform address with scalar loads into scalar registers, as it does the
+// kernel arguments; read through a generic pointer they come in as vector
+// loads (the launch's own stores might alias them) and every use needs a
+// v_readfirstlane.  The scalar cache is invalidated when a launch starts.
+// (The host pass of the compiler, which only checks these functions, has no
+// such address space.)
+#if defined(__HIP_DEVICE_COMPILE__)
+#define LBM_CONST_AS __attribute__((address_space(4)))
+#else
+#define LBM_CONST_AS
+#endif
+template <typename T>
+__device__ __forceinline__ const LBM_CONST_AS T* ro(const T* p) {
+    return (const LBM_CONST_AS T*)p;
 }
 
 }  // namespace lbm

@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "block.hpp"
 #include "fused.hpp"
 
 namespace lbm {
@@ -22,7 +23,8 @@ struct Ctx {
     double* side_f;
     unsigned side_mom_bytes, side_f_bytes;
     bool save_f;  // boundary nodes save pre-collision populations (Zhao-Yong)
-    double* partial;
+    MassPart* partial;
+    MassUnit mass;
     double* mom_out;
     const float* ref;  // init: density plane of the buffer being filled (or null)
     Phys<double> ph;  // converted to the compute type by the launcher
@@ -31,7 +33,7 @@ struct Ctx {
     int tile_h2, nsegs2, nstrips2, nblocks2;
     const int* node_link;
     const int* tile_order;  // two-step pass: tile of each workgroup
-    double* partial2;
+    MassPart* partial2;
     const int* lmeta;
     const double* lc;
     const double* luw;
@@ -50,6 +52,10 @@ void launch_main_f32(const Ctx& c, const void* src, void* dst, bool moments);
 // two steps per pass src -> dst (storage forms with FP32 or FP16
 // populations and one reference density; see fused.hpp)
 void launch_main2_f32(const Ctx& c, const void* src, void* dst);
+// several steps per launch (see block.hpp): 1024 lanes per tile (wide) or
+// 512; lds: bytes of dynamic LDS
+void launch_block_f64(const Ctx& c, const BlockArgs& a, bool wide, unsigned lds);
+void launch_block_f32(const Ctx& c, const BlockArgs& a, bool wide, unsigned lds);
 // one boundary pass on cur
 void launch_boundary_f64(const Ctx& c, void* cur, const BndArgs& b, int nblocks);
 void launch_boundary_f32(const Ctx& c, void* cur, const BndArgs& b, int nblocks);
@@ -59,10 +65,9 @@ void launch_init_f64(const Ctx& c, const double* rho_wall, const double* rho0,
                      const double* ux0, const double* uy0, void* buf, void* other);
 void launch_init_f32(const Ctx& c, const double* rho_wall, const double* rho0,
                      const double* ux0, const double* uy0, void* buf, void* other);
-// the last main pass's partials (two arrays if it made two steps) into
-// hist[(clock + 1) % cap], clock += 1 per step
-void launch_reduce(const Ctx& c, bool two, long long cap, long long* clock, double* hist,
-                   long long* unstable);
+// the last main pass's partials into hist[(clock + 1) % cap], clock += 1 per
+// step
+void launch_reduce(const Ctx& c, const MassPass& r);
 
 // One step of a batch: boundary and main passes (per storage precision),
 // then the per-instance reduction.

@@ -33,6 +33,7 @@ void main_t(const Ctx& c, const S* src, S* dst) {
     a.side_mom = c.side_mom;
     a.side_f = c.side_f;
     a.partial = c.partial;
+    a.mass = c.mass;
     a.mom_out = c.mom_out;
     a.nx = c.nx;
     a.ny = c.ny;
@@ -76,6 +77,7 @@ void main2_t(const Ctx& c, const S* src, S* dst) {
     a.side_mom = c.side_mom;
     a.partial1 = c.partial;
     a.partial2 = c.partial2;
+    a.mass = c.mass;
     a.lmeta = c.lmeta;
     a.lc = c.lc;
     a.luw = c.luw;

@@ -141,30 +141,31 @@ Ctx ctx(lbm_domain* d) {
     c.eos = d->eos;
     c.storage = d->storage;
     c.tile_w = d->tile_w;
-    c.tile_h = d->tile_h;
+    c.tile_h = seg_rows(d->tile_h);
     c.nsegs = d->nsegs;
     c.nstrips = d->nstrips;
     c.nblocks = d->nblocks;
     c.flags = d->flags;
     c.side_idx = d->side_idx;
     c.psiw = d->psiw;
-    c.side_mom = d->side_mom;
+    c.side_mom = d->side_mom[d->cur ^ 1];  // a pass writes those of the buffer it fills
     c.side_f = d->side_f;
     c.side_mom_bytes = (unsigned)(3 * std::max(d->nslots, 1) * 8);
     c.side_f_bytes = (unsigned)(9 * (d->save_f ? std::max(d->nslots, 1) : 1) * 8);
     c.save_f = d->save_f;
     c.partial = d->partial;
+    c.mass = d->mass;
     c.mom_out = d->mom_out;
     c.ref = nullptr;
     c.ph = d->ph64;
     c.stream = d->stream;
-    c.tile_h2 = d->tile_h2;
+    c.tile_h2 = seg_rows(d->tile_h2);
     c.nsegs2 = d->nsegs2;
     c.nstrips2 = d->nstrips2;
     c.nblocks2 = d->nblocks2;
     c.node_link = d->node_link;
     c.tile_order = d->tile_order;
-    c.partial2 = d->partial2;
+    c.partial2 = d->partial + d->partial_cap;
     c.lmeta = d->lmeta;
     c.lc = d->lc;
     c.luw = d->luw;
@@ -188,6 +189,26 @@ void launch_main(lbm_domain* d, const void* src, void* dst, bool moments,
 
 int link_blocks(const lbm_domain* d) { return (d->nslot_links + 255) / 256; }
 
+MassPass mass_pass(lbm_domain* d) {
+    MassPass r{};
+    r.steps = d->pending_steps;
+    if (d->pending_block) {
+        r.partial = d->block.partial[d->block.set];
+        r.np = d->block.ntiles;
+        r.stride = r.np;
+    } else {
+        r.partial = d->partial;
+        r.np = d->pending_steps == 2 ? d->nblocks2 : d->nblocks;
+        r.stride = d->partial_cap;
+    }
+    r.unit = d->mass.unit;
+    r.hist = d->hist;
+    r.cap = d->cap;
+    r.clock = d->clock;
+    r.unstable = d->unstable;
+    return r;
+}
+
 BndArgs bnd_args(lbm_domain* d) {
     BndArgs b{};
     b.nslot = d->nslot_links;
@@ -200,20 +221,14 @@ BndArgs bnd_args(lbm_domain* d) {
     b.lslotf = d->lslotf;
     b.lc = d->lc;
     b.luw = d->luw;
-    b.side_mom = d->side_mom;
+    b.side_mom = d->side_mom[d->cur];
     b.side_f = d->side_f;
     b.plane = d->plane;
     b.rref = d->ph64.rref;
     b.lref = d->lref;
     b.fix = d->fix;
-    b.partial = d->partial;
-    b.partial2 = d->pending_steps == 2 ? d->partial2 : nullptr;
-    b.np = d->pending_steps == 2 ? d->nblocks2 : d->nblocks;
-    b.hist = d->hist;
-    b.unstable = d->unstable;
+    b.prev = mass_pass(d);
     b.do_reduce = d->pending ? 1 : 0;
-    b.cap = d->cap;
-    b.clock = d->clock;
     b.force = d->force;
     b.negrest = d->negrest;
     b.degen = d->degen;
@@ -243,7 +258,7 @@ void launch_boundary(lbm_domain* d, void* cur, const hipEvent_t* ev = nullptr) {
 
 void reduce_pending(lbm_domain* d) {
     if (!d->pending) return;
-    launch_reduce(ctx(d), d->pending_steps == 2, d->cap, d->clock, d->hist, d->unstable);
+    launch_reduce(ctx(d), mass_pass(d));
     d->pending = false;
 }
 
@@ -298,8 +313,73 @@ void launch_pass(lbm_domain* d, bool two, hipEvent_t* rec) {
     d->t += two ? 2 : 1;
     d->pending = true;
     d->pending_steps = two ? 2 : 1;
+    d->pending_block = false;
     d->pending_t = d->t;
     d->last_fused = two;
+    d->replay_valid = false;
+}
+
+// Runs of steps go through k_block where the domain has a plan for it, also
+// with two steps per pass asked for; rows per tile asked for with them name
+// the two-step kernel.
+bool uses_blocks(const lbm_domain* d) {
+    return d->block.steps > 0 && !(d->fused == 2 && d->tile_h2_asked);
+}
+
+// k steps in one launch of k_block, which also records the masses of the
+// previous one.
+void launch_block(lbm_domain* d, int k) {
+    BlockPlan& p = d->block;
+    BlockArgs a{};
+    a.src = d->f[d->cur];
+    a.dst = d->f[d->cur ^ 1];
+    a.flags = d->flags;
+    a.psiw = d->psiw;
+    a.mom_in = d->side_mom[d->cur];
+    a.mom_out = d->side_mom[d->cur ^ 1];
+    a.prev = mass_pass(d);
+    a.do_reduce = d->pending ? 1 : 0;
+    p.set ^= 1;
+    a.partial = p.partial[p.set];
+    a.partial_stride = p.ntiles;
+    a.tiles = p.tiles;
+    a.links = p.links;
+    a.nodes = p.nodes;
+    a.lc = d->lc;
+    a.luw = d->luw;
+    a.negrest = d->negrest;
+    a.degen = d->degen;
+    a.fix = d->fix;
+    a.moving = p.moving ? 1 : 0;
+    a.chi = d->rule == LBM_RULE_HALFWAY || d->rule == LBM_RULE_FH || d->rule == LBM_RULE_MLS;
+    a.max_len = p.max_len;
+    a.nx = d->nx;
+    a.ny = d->ny;
+    a.pitch = d->pitch;
+    a.plane = d->plane;
+    a.steps = k;
+    a.halo = p.halo;
+    a.pull = p.pull;
+    a.nstrips = p.nstrips;
+    a.nsegs = p.nsegs;
+    a.ntiles = p.ntiles;
+    a.max_nodes = p.max_nodes;
+    a.open_x = d->open_x;
+    a.inlet_u = d->inlet_u;
+    a.mass = d->mass;
+    a.mom_bytes = (unsigned)(3 * std::max(d->nslots, 1) * 8);
+    a.link_bytes = p.link_bytes;
+    a.node_bytes = p.node_bytes;
+    const unsigned lds = block_lds(p.max_nodes);
+    if (d->storage == LBM_STORE_F64) launch_block_f64(ctx(d), a, p.wide, lds);
+    else launch_block_f32(ctx(d), a, p.wide, lds);
+    d->cur ^= 1;
+    d->t += k;
+    d->pending = true;
+    d->pending_steps = k;
+    d->pending_block = true;
+    d->pending_t = d->t;
+    d->last_fused = false;
     d->replay_valid = false;
 }
 
@@ -385,6 +465,21 @@ hipGraphExec_t step_graph(lbm_domain* d, int parity, int level) {
 int run_steps(lbm_domain* d, int64_t n) {
     reduce_pending(d);  // every run below starts with no mass pending
     if (d->prof > 0) return run_steps_profiled(d, n);
+    if (uses_blocks(d) && n > 1) {
+        // the last step is a pass of its own: it leaves f*(t - 1) with the
+        // ghosts of step t and the wall force, which the read-outs use
+        while (n > 1) {
+            const int k = (int)std::min<int64_t>(n - 1, d->block.steps);
+            // (a launch of one step costs more than a pass, but for the
+            // smallest domains, where the launches are the cost)
+            if (k == 1 && !d->block.wide) launch_pass(d, false, nullptr);
+            else launch_block(d, k);
+            n -= k;
+        }
+        launch_pass(d, false, nullptr);
+        reduce_pending(d);
+        return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
+    }
     while (n > 0) {
         int level = lbm_domain::kGraphLevels - 1;
         while ((1LL << level) > n) --level;
@@ -392,8 +487,10 @@ int run_steps(lbm_domain* d, int64_t n) {
         if (!d->graphs[d->cur][level] && !d->graphs_off) {
             // all runs for both parities at once, so that later calls of
             // any length replay without capturing
+            // (with k_block only single steps come here)
+            const int levels = uses_blocks(d) ? 1 : lbm_domain::kGraphLevels;
             for (int par = 0; par < 2; ++par)
-                for (int lv = 0; lv < lbm_domain::kGraphLevels; ++lv) (void)step_graph(d, par, lv);
+                for (int lv = 0; lv < levels; ++lv) (void)step_graph(d, par, lv);
         }
         hipGraphExec_t g = d->graphs_off ? nullptr : d->graphs[d->cur][level];
         if (g) {
@@ -433,7 +530,8 @@ int check_unstable(lbm_domain* d) {
 // x0 + 59).  Only the order changes: every tile writes its own partials.
 int order_tiles(lbm_domain* d) {
     if (!d->tile_order) return LBM_OK;
-    const int ns = d->nstrips2, ng = d->nsegs2, n = d->nblocks2, H = d->tile_h2;
+    const int ns = d->nstrips2, ng = d->nsegs2, n = d->nblocks2;
+    const int H = seg_rows(d->tile_h2);
     const int nx = d->nx, ny = d->ny;
     std::vector<long long> w((size_t)n, 0);
     auto wrap = [](long long v, long long m) { return (int)(((v % m) + m) % m); };
@@ -473,6 +571,231 @@ struct LinkRec {
     int dir;
     int src;   // index in the descriptor
 };
+
+// Nodes a pull reaches (x_ff of the quadratic interpolation lies two away),
+// and a whole step of k_block.
+int block_pull(const lbm_domain* d) { return d->rule == LBM_RULE_IBB_QUADRATIC ? 2 : 1; }
+int block_reach(const lbm_domain* d) { return block_pull(d) + (d->eos == EOS_NONE ? 0 : 1); }
+
+// Tables of k_block for `steps` steps per launch: per tile the cut links
+// whose fluid node its region pulls, grouped by node in chunks of 64, and the
+// nodes whose moments they read.  False if a tile holds more than a workgroup
+// has lanes or LDS for.
+struct BlockTables {
+    int steps = 0, halo = 0, pull = 0, nstrips = 0, nsegs = 0, max_nodes = 0, max_len = 0;
+    std::vector<BlockTile> tiles;
+    std::vector<BlockLink> links;
+    std::vector<BlockNode> nodes;
+};
+bool block_tables(const lbm_domain* d, int steps, const std::vector<int>& lnode,
+                  const std::vector<int>& lmeta, const std::vector<int>& lslotb,
+                  const std::vector<int>& lslotf, const std::vector<double>& lc,
+                  BlockTables& b) {
+    b = BlockTables{};
+    b.steps = steps;
+    b.pull = block_pull(d);
+    b.halo = steps * block_reach(d);
+    const int ow = kBlockW - 2 * b.halo, oh = kBlockH - 2 * b.halo;
+    if (ow < 1 || oh < 1) return false;
+    b.nstrips = (d->nx + ow - 1) / ow;
+    b.nsegs = (d->ny + oh - 1) / oh;
+    if ((long long)b.nstrips * b.nsegs >= (1 << 24)) return false;
+    // the regions (and the place in them) that pull a column or row
+    auto places = [&](int n, int parts, int width) {
+        std::vector<std::vector<std::pair<int, int>>> v((size_t)n);
+        for (int s = 0; s < parts; ++s) {
+            const int x0 = (int)((long long)s * n / parts);
+            for (int l = b.pull; l < width - b.pull; ++l)
+                v[(size_t)wrapi(x0 - b.halo + l, n)].push_back({s, l});
+        }
+        return v;
+    };
+    const auto X = places(d->nx, b.nstrips, kBlockW), Y = places(d->ny, b.nsegs, kBlockH);
+    auto tile_of = [&](int strip, int seg) {
+        const int band = seg / 8, h = std::min(8, b.nsegs - 8 * band);
+        return band * 8 * b.nstrips + strip * h + (seg - 8 * band);
+    };
+    struct Image {
+        int k0, at;  // first link of the node, local index
+    };
+    const int nt = b.nstrips * b.nsegs, P = d->pitch;
+    std::vector<int> first((size_t)nt + 1, 0);
+    auto images = [&](auto&& take) {
+        for (size_t k = 0; k < lnode.size();) {
+            if (((lmeta[k] >> 4) & 15) == LK_PAD) {
+                ++k;
+                continue;
+            }
+            for (const auto& y : Y[(size_t)(lnode[k] / P)])
+                for (const auto& x : X[(size_t)(lnode[k] % P)])
+                    take(tile_of(x.first, y.first), (int)k, y.second * kBlockW + x.second);
+            k += (size_t)((lmeta[k] >> 8) & 15);
+        }
+    };
+    images([&](int tile, int, int) { ++first[(size_t)tile + 1]; });
+    for (int i = 0; i < nt; ++i) first[(size_t)i + 1] += first[(size_t)i];
+    std::vector<Image> im((size_t)first[(size_t)nt]);
+    {
+        std::vector<int> at(first.begin(), first.end() - 1);
+        images([&](int tile, int k, int l) { im[(size_t)at[(size_t)tile]++] = Image{k, l}; });
+    }
+    std::vector<int> rec(kBlockW * kBlockH, -1);
+    b.tiles.resize((size_t)nt);
+    for (int i = 0; i < nt; ++i) {
+        const int2 g = block_place(i, b.nstrips, b.nsegs);
+        const int x0 = (int)((long long)g.x * d->nx / b.nstrips);
+        const int y0 = (int)((long long)g.y * d->ny / b.nsegs);
+        const int x1 = (int)((long long)(g.x + 1) * d->nx / b.nstrips);
+        const int y1 = (int)((long long)(g.y + 1) * d->ny / b.nsegs);
+        auto own = [&](int l) {
+            const int lx = l % kBlockW - b.halo, ly = l / kBlockW - b.halo;
+            return lx >= 0 && lx < x1 - x0 && ly >= 0 && ly < y1 - y0;
+        };
+        const int link0 = (int)b.links.size(), node0 = (int)b.nodes.size();
+        auto record = [&](int l, int slot) {
+            if (rec[(size_t)l] < 0) {
+                rec[(size_t)l] = (int)b.nodes.size() - node0;
+                b.nodes.push_back(BlockNode{slot, (unsigned short)l, (unsigned char)own(l), 0});
+            }
+            return rec[(size_t)l];
+        };
+        BlockLink pad{};
+        pad.meta = LK_PAD << 4 | 1;
+        pad.xb = 2 * kBlockW + 2;
+        for (int e = first[(size_t)i]; e < first[(size_t)i + 1]; ++e) {
+            const int k0 = im[(size_t)e].k0, l = im[(size_t)e].at;
+            const int len = (lmeta[(size_t)k0] >> 8) & 15;
+            b.max_len = std::max(b.max_len, len);
+            const int used = ((int)b.links.size() - link0) % 64;
+            if (used + len > 64) b.links.resize(b.links.size() + (size_t)(64 - used), pad);
+            const int sb = record(l, lslotb[(size_t)k0]);
+            b.nodes[(size_t)(node0 + sb)].bnd = 1;
+            for (int k = k0; k < k0 + len; ++k) {
+                const int a = lmeta[(size_t)k] & 15;
+                int sf = 0;
+                if (lslotf[(size_t)k] >= 0)
+                    sf = record(l - cx(a) - cy(a) * kBlockW, lslotf[(size_t)k]);
+                BlockLink r{};
+                r.meta = lmeta[(size_t)k];
+                r.id = k;
+                r.xb = (unsigned short)l;
+                r.sb = (unsigned short)sb;
+                r.sf = (unsigned short)sf;
+                r.own = (unsigned short)own(l);
+                const double* const c = lc.data() + 8 * (size_t)k;
+                const bool chi = ((lmeta[(size_t)k] >> 4) & 15) <= LK_CHI_EXT;
+                r.k[0] = chi ? c[3] : c[0];
+                r.k[1] = chi ? c[4] : c[1];
+                b.links.push_back(r);
+            }
+        }
+        const int used = ((int)b.links.size() - link0) % 64;
+        if (used) b.links.resize(b.links.size() + (size_t)(64 - used), pad);
+        const int chunks = ((int)b.links.size() - link0) / 64;
+        const int nn = (int)b.nodes.size() - node0;
+        for (int k = node0; k < node0 + nn; ++k) rec[(size_t)b.nodes[(size_t)k].at] = -1;
+        if (chunks > kBlockThreads / 64 || nn > kBlockNodes || b.links.size() >= (1u << 25))
+            return false;
+        b.max_nodes = std::max(b.max_nodes, nn);
+        b.tiles[(size_t)i] = BlockTile{link0, chunks, node0, nn};
+    }
+    return true;
+}
+
+// Estimated time of a step in us: single steps (boundary and main launch), and
+// launches of k_block with `steps` steps on `tiles` tiles.  Fitted to measured
+// steps of droplets (64^2 to 2048^2) and of the static channel; what matters
+// is where the curves cross.
+//   single: two launches and the populations at 4.6 TB/s (FP16 at 3.7);
+//     measured in FP64 / FP32 / FP16 storage: 13.3 / 12.2 / 12 at 400^2,
+//     31.4 / 24.7 / 20 at 1024^2, 132 / 75 / 48 at 2048^2.
+//   k_block: 6.6 us a launch and 3.3 a step while every tile has a CU of its
+//     own, then a cost per further tile, of which the two-phase step, FP64
+//     arithmetic and the halos (a step more shrinks the tiles) are the parts.
+//     Measured for the droplet in FP64 storage: 6 steps at 128^2 4.4 a step,
+//     3 at 400^2 7.6, 2 at 1024^2 26.3, 2 at 2048^2 96; in FP32 storage with
+//     FP64 arithmetic 18.2 at 800^2, 24.9 at 1024^2, 80 at 2048^2 (arithmetic
+//     of the halos: single steps are faster from 1024^2 on).
+double single_us(const lbm_domain* d) {
+    const double mb = 18.0 * (double)d->esize * (double)d->fluid * 1e-6;
+    return 8.0 + mb / (d->esize == 2 ? 3.7 : 4.6);
+}
+double block_us(const lbm_domain* d, int steps, long long tiles, int ncu) {
+    const bool two_phase = d->eos != EOS_NONE;
+    const bool arith64 = d->storage == LBM_STORE_F64 || d->storage == LBM_STORE_F32;
+    double us = 6.6 + 3.3 * steps;
+    if (tiles > ncu) {
+        const double per = two_phase ? (arith64 ? 0.0175 + 0.0037 * steps : 0.0105 + 0.0031 * steps)
+                                     : (d->esize == 8 ? 0.0245 + 0.0023 * steps
+                                                      : 0.0145 + 0.0040 * steps);
+        us += 5.0 + per * (double)(tiles - ncu);
+    }
+    return us / steps;
+}
+
+// Whether and how the domain's runs go through k_block: the number of steps
+// per launch with the least estimated time, if that is below single steps'.
+// (Zhao-Yong needs the pre-collision populations of the step before, and the
+// FP16 per-node form a second plane; both stay with single steps.)
+int plan_blocks(lbm_domain* d, const std::vector<int>& lnode, const std::vector<int>& lmeta,
+                const std::vector<int>& lslotb, const std::vector<int>& lslotf,
+                const std::vector<double>& lc) {
+    if (d->arena || d->storage == LBM_STORE_F16NODE || d->rule == LBM_RULE_ZHAO_YONG)
+        return LBM_OK;
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return LBM_EDEVICE;
+    int steps = 0;
+    double best = single_us(d);
+    for (int k = 2; k <= kBlockSteps; ++k) {
+        const int halo = k * block_reach(d);
+        const int ow = kBlockW - 2 * halo, oh = kBlockH - 2 * halo;
+        if (ow < 4 || oh < 4) break;
+        const long long n = (long long)((d->nx + ow - 1) / ow) * ((d->ny + oh - 1) / oh);
+        const double us = block_us(d, k, n, ncu);
+        if (us < best) {
+            best = us;
+            steps = k;
+        }
+    }
+    BlockTables b;
+    if (steps == 0 || !block_tables(d, steps, lnode, lmeta, lslotb, lslotf, lc, b)) return LBM_OK;
+    BlockPlan& p = d->block;
+    int rc;
+    if ((rc = upload(d, &p.tiles, b.tiles)) || (rc = upload(d, &p.links, b.links)) ||
+        (rc = upload(d, &p.nodes, b.nodes)))
+        return rc;
+    const int nt = b.nstrips * b.nsegs;
+    for (MassPart*& q : p.partial)
+        if ((rc = dev_alloc(d, (void**)&q, (size_t)steps * nt * sizeof(MassPart)))) return rc;
+    if (hipStreamSynchronize(d->stream) != hipSuccess) return LBM_EDEVICE;  // the tables end here
+    p.halo = b.halo;
+    p.pull = b.pull;
+    p.nstrips = b.nstrips;
+    p.nsegs = b.nsegs;
+    p.ntiles = nt;
+    p.wide = nt <= ncu;
+    p.max_nodes = b.max_nodes;
+    p.max_len = b.max_len;
+    p.link_bytes = (unsigned)(b.links.size() * sizeof(BlockLink));
+    p.node_bytes = (unsigned)(b.nodes.size() * sizeof(BlockNode));
+    p.steps = steps;
+    return LBM_OK;
+}
+
+// The unit of the mass sums (see MassUnit) from the largest initial density.
+MassUnit mass_unit(const lbm_desc* s, long long n) {
+    double mx = 0.0;
+    for (long long i = 0; i < n; ++i)
+        if (!s->solid[i] && s->rho0[i] > mx) mx = s->rho0[i];
+    // (a range in which neither the unit nor its multiples leave FP64)
+    mx = std::min(std::max(mx, 1e-200), 1e200);
+    int e = 0;
+    (void)std::frexp(mx, &e);  // mx < 2^e
+    const double unit = std::ldexp(1.0, e - 40);
+    return MassUnit{1.5 * std::ldexp(unit, 52), unit, 1.0 / unit};
+}
 
 int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     const int nx = s->nx, ny = s->ny;
@@ -550,6 +873,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
                         s->rule == LBM_RULE_MLS))
             return LBM_EINVAL;
         if (moving && s->fix == LBM_FIX_BAO) return LBM_EINVAL;
+        if (moving) d->block.moving = true;
         if (s->rule == LBM_RULE_FH && l.q < 0.5 && std::fabs(s->tau - 1.0) < 1e-12)
             singular = true;
         recs[k] = LinkRec{(int)b, l.dir, (int)k};
@@ -580,6 +904,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
             return LBM_EINVAL;
     }
     d->fluid = fluid;
+    d->mass = mass_unit(s, N);
     if (s->storage == LBM_STORE_F32DEV || s->storage == LBM_STORE_F16DEV) {
         double rref = s->rho_ref;
         if (rref == 0.0 && fluid > 0) {
@@ -610,7 +935,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     d->tile_w = s->tile_w ? s->tile_w : default_tile_w(nx);
     d->tile_h = s->tile_h ? s->tile_h : 9;  // rows come in rotations of three
     d->nstrips = (nx + strip_cols(d->tile_w) - 1) / strip_cols(d->tile_w);
-    d->nsegs = (ny + d->tile_h - 1) / d->tile_h;
+    d->nsegs = seg_count(ny, d->tile_h);
     d->nblocks = d->nstrips * d->nsegs;
     // two steps per pass: FP32 or FP16 populations with one reference
     // density, periodic, any rule but Zhao-Yong (which needs the
@@ -625,7 +950,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     d->fused = 1;  // two steps per pass on request (lbm_set_steps_per_pass)
     d->tile_h2 = kTileH2;
     d->nstrips2 = (nx + kF2Cols - 1) / kF2Cols;
-    d->nsegs2 = (ny + d->tile_h2 - 1) / d->tile_h2;
+    d->nsegs2 = seg_count(ny, d->tile_h2);
     d->nblocks2 = d->nstrips2 * d->nsegs2;
     d->cap = s->history_capacity > 0 ? s->history_capacity : (1LL << 20);
     d->stream = static_cast<hipStream_t>(s->stream);
@@ -810,7 +1135,11 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if ((rc = upload(d, &d->flags, flags))) return rc;
     if ((rc = upload(d, &d->side_idx, side_idx))) return rc;
     if (d->esize == 2 && (rc = dev_alloc(d, (void**)&d->psiw, (size_t)P * ny * 4))) return rc;
-    if ((rc = dev_alloc(d, (void**)&d->side_mom, (size_t)3 * std::max(nslots, 1) * 8))) return rc;
+    // (the passes of a batch write the moments in place)
+    for (int k = 0; k < (d->arena ? 1 : 2); ++k)
+        if ((rc = dev_alloc(d, (void**)&d->side_mom[k], (size_t)3 * std::max(nslots, 1) * 8)))
+            return rc;
+    if (d->arena) d->side_mom[1] = d->side_mom[0];
     if ((rc = dev_alloc(d, (void**)&d->side_f,
                         (size_t)9 * (d->save_f ? std::max(nslots, 1) : 1) * 8)))
         return rc;
@@ -819,9 +1148,10 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if (d->fusable)  // and for two-step tiles down to kMinTileH2 rows
         d->partial_cap = std::max(d->partial_cap,
                                   d->nstrips2 * ((ny + kMinTileH2 - 1) / kMinTileH2));
-    if ((rc = dev_alloc(d, (void**)&d->partial, (size_t)d->partial_cap * 8))) return rc;
+    if ((rc = dev_alloc(d, (void**)&d->partial,
+                        (size_t)(d->fusable ? 2 : 1) * d->partial_cap * sizeof(MassPart))))
+        return rc;
     if (d->fusable) {
-        if ((rc = dev_alloc(d, (void**)&d->partial2, (size_t)d->partial_cap * 8))) return rc;
         if ((rc = upload(d, &d->node_link, node_link))) return rc;
         if ((rc = dev_alloc(d, (void**)&d->tile_order, (size_t)d->partial_cap * 4))) return rc;
         if ((rc = order_tiles(d))) return rc;
@@ -848,6 +1178,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if ((rc = upload(d, &d->lc, lc))) return rc;
     if ((rc = upload(d, &d->luw, luw))) return rc;
     if (!lref.empty() && (rc = upload(d, &d->lref, lref))) return rc;
+    if ((rc = plan_blocks(d, lnode, lmeta, lslotb, lslotf, lc))) return rc;
     if ((rc = dev_alloc(d, (void**)&d->force,
                         (size_t)2 * std::max(link_blocks(d), 1) * 8)))
         return rc;
@@ -892,6 +1223,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
         }
         launch_init_f32(c, drw, dr0, du0, dv0, d->f[1], d->f[0]);
     }
+    d->cur = 1;
     launch_main(d, d->f[1], d->f[0], false);
     // the replay buffer starts as a copy, so that its solid nodes hold
     // psi of the wall density in their rest slots as the state buffers do
@@ -901,6 +1233,8 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     d->cur = 0;
     d->t = 0;
     d->pending = true;
+    d->pending_steps = 1;
+    d->pending_block = false;
     d->pending_t = 0;
     reduce_pending(d);
     if (hipGetLastError() != hipSuccess) return LBM_EDEVICE;
@@ -936,7 +1270,7 @@ int domain_set_tiles(lbm_domain* d, int tile_w, int tile_h) {
     if (tile_w != 64 && tile_w != 128 && tile_w != 256) return LBM_EINVAL;
     if (tile_h < 1) return LBM_EINVAL;
     const int sc = strip_cols(tile_w);
-    const int ns = (d->nx + sc - 1) / sc, ng = (d->ny + tile_h - 1) / tile_h;
+    const int ns = (d->nx + sc - 1) / sc, ng = seg_count(d->ny, tile_h);
     if ((long long)ns * ng > d->partial_cap) return LBM_EINVAL;
     drop_graphs(d);
     d->tile_w = tile_w;
@@ -1177,7 +1511,8 @@ int lbm_get_state(lbm_domain* d, void* buf, size_t* bytes) {
     p += fb;
     if (hipMemcpy(p, d->f[d->cur ^ 1], fb, hipMemcpyDeviceToHost) != hipSuccess) return LBM_EDEVICE;
     p += fb;
-    if (hipMemcpy(p, d->side_mom, sm, hipMemcpyDeviceToHost) != hipSuccess) return LBM_EDEVICE;
+    if (hipMemcpy(p, d->side_mom[d->cur], sm, hipMemcpyDeviceToHost) != hipSuccess)
+        return LBM_EDEVICE;
     p += sm;
     if (hipMemcpy(p, d->side_f, sf, hipMemcpyDeviceToHost) != hipSuccess) return LBM_EDEVICE;
     p += sf;
@@ -1209,7 +1544,7 @@ int lbm_set_state(lbm_domain* d, const void* buf, size_t bytes) {
     p += fb;
     if (hipMemcpy(d->f[1], p, fb, hipMemcpyHostToDevice) != hipSuccess) return LBM_EDEVICE;
     p += fb;
-    if (hipMemcpy(d->side_mom, p, sm, hipMemcpyHostToDevice) != hipSuccess) return LBM_EDEVICE;
+    if (hipMemcpy(d->side_mom[0], p, sm, hipMemcpyHostToDevice) != hipSuccess) return LBM_EDEVICE;
     p += sm;
     if (hipMemcpy(d->side_f, p, sf, hipMemcpyHostToDevice) != hipSuccess) return LBM_EDEVICE;
     p += sf;
@@ -1271,8 +1606,9 @@ int lbm_set_steps_per_pass(lbm_domain* d, int32_t steps, int32_t tile_h) {
     if (steps == 2 && !d->fusable) return LBM_EINVAL;
     const int th = tile_h ? tile_h : kTileH2;
     if (steps == 2) {
+        d->tile_h2_asked = tile_h > 0;
         if (th < kMinTileH2) return LBM_EINVAL;
-        const int ng = (d->ny + th - 1) / th;
+        const int ng = seg_count(d->ny, th);
         if ((long long)d->nstrips2 * ng > d->partial_cap) return LBM_EINVAL;
         d->tile_h2 = th;
         d->nsegs2 = ng;

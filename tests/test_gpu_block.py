@@ -1,0 +1,111 @@
+"""Several steps per launch on LDS blocks (k_block) against single steps:
+with kernel timing on, every step is a pass of its own; without, runs go
+through k_block where the domain has a plan for it.  Fields, masses, wall
+force, counters and the first unstable step are the same bit for bit, at
+lattices narrower than a block's region, at multiples of a tile and one node
+either side, for every rule, fix, EOS and storage form, and the total mass has
+the same bits for every tile shape."""
+import sys
+
+import numpy as np
+import pytest
+
+from lbm_inputs import configs as cfg
+
+from tests._random_cases import random_case
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def L():
+    from paper_1908_09235_amd import lbm
+    lbm.lib()
+    return lbm
+
+
+RUNS = (1, 2, 3, 7, 26, 1, 8)
+
+
+def _same(L, p, storage, runs=RUNS, **kw):
+    with L.Domain(p, storage=storage, history_capacity=256, **kw) as a, \
+            L.Domain(p, storage=storage, history_capacity=256, **kw) as b:
+        L.lbm_set_profiling(a.h, 1)  # single steps
+        for n in runs:
+            for d in (a, b):
+                try:
+                    d.step(n)
+                except L.LbmError as e:
+                    assert e.code == L.LBM_EUNSTABLE
+            tag = (p.name, storage, a.t)
+            assert a.t == b.t
+            for x, y in zip(a.moments(), b.moments()):
+                assert np.array_equal(x, y, equal_nan=True), tag
+            assert np.array_equal(a.mass_history(), b.mass_history(), equal_nan=True), tag
+            assert np.array_equal(a.wall_force(), b.wall_force(), equal_nan=True), tag
+        assert a.negative_rest() == b.negative_rest()
+        assert a.degenerate_b() == b.degenerate_b()
+        assert L.lbm_unstable_step(a.h) == L.lbm_unstable_step(b.h)
+
+
+STORAGES = ["f64", "f32", "f32_arith32", "f32dev", "f16dev"]
+
+
+@pytest.mark.parametrize("storage", STORAGES)
+@pytest.mark.parametrize("case", [
+    ("mls", "A"), ("mls", "B"), ("mls", "bao"), ("fh", "B"), ("halfway", "none"),
+    ("ibb_linear", "A"), ("ibb_quadratic", "A"), ("zhao_yong", "none")])
+def test_every_rule(L, case, storage):
+    p = cfg.droplet_on_cylinder(rule=case[0], fix=case[1], tau=0.8, collision="mrt",
+                                rho_wall=0.05, name="_".join(case))
+    say(f"[gpu] blocks vs single steps {case} {storage}")
+    _same(L, p, storage)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f16dev"])
+@pytest.mark.parametrize("nx,ny", [(3, 3), (5, 40), (31, 33), (32, 32), (48, 24), (96, 95),
+                                   (97, 96), (289, 97)])
+def test_sizes_around_a_tile(L, nx, ny, storage):
+    say(f"[gpu] blocks vs single steps {nx}x{ny} {storage}")
+    p = cfg.free_droplet(max(nx, ny), 0.25 * min(nx, ny), eos="exp")
+    rho0 = np.ascontiguousarray(p.rho0[:ny, :nx])
+    _same(L, p.with_(nx=nx, ny=ny, solid=np.zeros((ny, nx), np.uint8), rho0=rho0,
+                     rho_wall=np.ones((ny, nx))), storage)
+
+
+@pytest.mark.parametrize("make", [
+    lambda: cfg.couette(10, rule="mls", fix="A"),              # moving walls
+    lambda: cfg.cylinder_flow(20.0, fix="B", d=8.0),           # open x
+    lambda: cfg.sloped_channel(16, fix="B", g0=1e-3),          # walls through every tile
+    lambda: cfg.static_gravity(0.3, rule="mls", fix="A", nx=40, ny=30),
+    lambda: cfg.cfg2a(scale=5.0)])                             # more tiles than CUs
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+def test_flows(L, make, storage):
+    p = make()
+    say(f"[gpu] blocks vs single steps {p.name} {storage}")
+    _same(L, p, storage)
+
+
+@pytest.mark.parametrize("k", range(12))
+def test_random_cases(L, k):
+    p = random_case(k)[0]
+    say(f"[gpu] blocks vs single steps random {k} {p.nx}x{p.ny} {p.rule}/{p.fix}")
+    _same(L, p, STORAGES[k % 5])
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32dev", "f16node"])
+def test_mass_does_not_depend_on_the_tiles(L, storage):
+    p = cfg.cfg1("mls", "B")
+    got = []
+    for tw, th in ((64, 3), (128, 16), (256, 7), (256, 4000)):
+        with L.Domain(p, storage=storage, tile_w=tw, tile_h=th, history_capacity=64) as d:
+            L.lbm_set_profiling(d.h, 1)
+            d.step(20)
+            got.append(d.mass_history())
+    say(f"[gpu] masses for four tile shapes, {storage}: {got[0][-1]!r}")
+    assert all(np.array_equal(got[0], g) for g in got[1:])
