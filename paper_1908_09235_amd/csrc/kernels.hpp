@@ -140,7 +140,7 @@ struct MainArgs {
     double* __restrict__ side_mom;      // [slot][3]: rho, ux, uy
     double* __restrict__ side_f;        // [slot][9]: pre-collision f
     MassPart* __restrict__ partial;     // per workgroup
-    double* __restrict__ mom_out;       // moments mode: rho, ux, uy planes
+    double* mom_out[3];                 // moments mode: rho, ux, uy (null: not wanted)
     int nx, ny, pitch;
     long long plane;                    // elements per population plane
     int tile_h, nsegs, nstrips;
@@ -454,10 +454,11 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
             if (upd && k < H) {
                 const bool fl = live;
                 const long long o = (long long)y * a.nx + x;
-                const long long n2 = (long long)a.nx * a.ny;
-                a.mom_out[o] = fl ? (DEV == 1 ? double(ph.rref) + double(drho) : double(rho)) : 0.0;
-                a.mom_out[n2 + o] = fl ? double(ux) : 0.0;
-                a.mom_out[2 * n2 + o] = fl ? double(uy) : 0.0;
+                if (a.mom_out[0])
+                    a.mom_out[0][o] = fl ? (DEV == 1 ? double(ph.rref) + double(drho) : double(rho))
+                                         : 0.0;
+                if (a.mom_out[1]) a.mom_out[1][o] = fl ? double(ux) : 0.0;
+                if (a.mom_out[2]) a.mom_out[2][o] = fl ? double(uy) : 0.0;
             }
         } else {
             // FP64 density (the deviation forms add the reference here)
@@ -1063,7 +1064,7 @@ __device__ __forceinline__ MainArgs<S> inst_main_args(const I_t& I, long long t,
     a.mass.magic = I.mass.magic;
     a.mass.unit = I.mass.unit;
     a.mass.inv = I.mass.inv;
-    a.mom_out = nullptr;
+    for (double*& p : a.mom_out) p = nullptr;
     a.nx = I.nx;
     a.ny = I.ny;
     a.pitch = I.pitch;

@@ -25,7 +25,7 @@ struct Ctx {
     bool save_f;  // boundary nodes save pre-collision populations (Zhao-Yong)
     MassPart* partial;
     MassUnit mass;
-    double* mom_out;
+    double* mom_out[3];  // moments mode: rho, ux, uy planes (null: not wanted)
     const float* ref;  // init: density plane of the buffer being filled (or null)
     Phys<double> ph;  // converted to the compute type by the launcher
     hipStream_t stream;

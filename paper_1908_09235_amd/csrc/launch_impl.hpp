@@ -34,7 +34,7 @@ void main_t(const Ctx& c, const S* src, S* dst) {
     a.side_f = c.side_f;
     a.partial = c.partial;
     a.mass = c.mass;
-    a.mom_out = c.mom_out;
+    for (int k = 0; k < 3; ++k) a.mom_out[k] = c.mom_out[k];
     a.nx = c.nx;
     a.ny = c.ny;
     a.pitch = c.pitch;

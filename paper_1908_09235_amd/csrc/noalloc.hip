@@ -43,7 +43,7 @@ double* scratch_on(int dev) {
 int moments_into(lbm_domain* d, double* sp, double* rho, double* ux, double* uy) {
     const size_t nn = (size_t)d->nx * d->ny;
     Ctx c = domain_ctx(d);
-    c.mom_out = sp;
+    for (int k = 0; k < 3; ++k) c.mom_out[k] = sp + k * nn;
     // the pre-collision moments at t are pulled from f*(t - 1)
     const void* src = moments_source(d);
     if (d->storage == LBM_STORE_F64) launch_main_f64(c, src, nullptr, true);
