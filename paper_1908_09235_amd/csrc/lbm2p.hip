@@ -83,19 +83,42 @@ void free_domain(lbm_domain* d) {
 
 inline int wrapi(int i, int n) { return ((i % n) + n) % n; }
 
-// The widest workgroup whose share of lanes that update a node is within
-// 10 % of the best width's (wider strips re-read fewer halo columns and
-// measure faster at equal share).
-int default_tile_w(int nx) {
+// Rows per tile.  A tile's rows are worked one after another, in rotations of
+// three, so a lattice with few tiles lasts as long as one tile: it is cut into
+// as many as the chip holds wavefronts for (4 a SIMD, 4096 in all), each row
+// of halos more being a cost only once the chip is full.  Main and boundary
+// launch, us a step, 64 columns by 3 / 6 / 9 rows and the former default (9
+// rows, the width below), droplet in FP64 storage (FP32): 128^2 11.1 / 13.9 /
+// 16.8 and 16.8; 400^2 13.3 / 15.9 / 18.7 and 18.7 (12.2 / 15.2 / 18.4); 600 x
+// 500 17.0 / 17.8 / 20.6 and 23.9; 800^2 24.6 / 23.2 / 25.8 and 25.6 (20.8 /
+// 21.0 / 24.2 and 24.8); 1024^2 33.0 / 31.4 / 31.9 and 31.7 (26.3 / 24.7 /
+// 25.2 and 29.3); 1500 x 1400 77.8 / 73.0 / 72.4 and 71.2.
+constexpr long long kSmallNodes = 500000;   // 3 rows
+constexpr long long kMediumNodes = 1200000; // 6 rows
+int default_tile_h(int nx, int ny) {
+    const long long n = (long long)nx * ny;
+    return n <= kSmallNodes ? 3 : n <= kMediumNodes ? 6 : 9;
+}
+
+// Columns per tile: 64 where there are few tiles (above).  Otherwise the
+// widest workgroup whose share of lanes that update a node is within 10 % of
+// the best width's (wider strips re-read fewer halo columns and measure
+// faster at equal share); within 2 % for the FP16 per-node form, whose rings
+// of densities make idle lanes dearer (2048^2: 68.9 us a step with 256 columns
+// and a share of 0.89, 62.2 with 128 and 0.94; 3999 x 2001, 0.98 either way:
+// 109.1 and 111.4).
+int default_tile_w(int nx, int ny, int storage) {
+    if ((long long)nx * ny <= kMediumNodes) return 64;
     double eff[3], best = 0.0;
     const int ws[3] = {256, 128, 64};
+    const double near = storage == LBM_STORE_F16NODE ? 0.98 : 0.9;
     for (int k = 0; k < 3; ++k) {
         const int ns = (nx + strip_cols(ws[k]) - 1) / strip_cols(ws[k]);
         eff[k] = (double)nx / ((double)ns * ws[k]);
         best = std::max(best, eff[k]);
     }
     for (int k = 0; k < 3; ++k)
-        if (eff[k] >= 0.9 * best) return ws[k];
+        if (eff[k] >= near * best) return ws[k];
     return 64;
 }
 
@@ -933,8 +956,8 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     d->fix = s->fix;
     d->open_x = s->open_x;
     d->inlet_u = s->open_x ? s->inlet_u : 0.0;
-    d->tile_w = s->tile_w ? s->tile_w : default_tile_w(nx);
-    d->tile_h = s->tile_h ? s->tile_h : 9;  // rows come in rotations of three
+    d->tile_w = s->tile_w ? s->tile_w : default_tile_w(nx, ny, d->storage);
+    d->tile_h = s->tile_h ? s->tile_h : default_tile_h(nx, ny);
     d->nstrips = (nx + strip_cols(d->tile_w) - 1) / strip_cols(d->tile_w);
     d->nsegs = seg_count(ny, d->tile_h);
     d->nblocks = d->nstrips * d->nsegs;
