@@ -318,9 +318,12 @@ const char *lbm_status_string(int status);
  * what lbm_step computes for it alone.  All instances of a batch share the
  * storage form and the EOS kind.  Device memory for all of them comes from
  * one arena allocated at creation; instances are built on a stream of the
- * batch's own while earlier work runs on the compute stream.  A step of the
- * batch is three launches over all instances (boundary pass, main pass,
- * per-instance mass reduction), replayed from a captured HIP graph.
+ * batch's own while earlier work runs on the compute stream.  Runs go through
+ * launches of several steps over all instances where that is faster (their
+ * tables lie outside the arena, in an eighth of its size within 4 to 256 MiB);
+ * other steps, and the last of a run, are three launches (boundary pass, main
+ * pass, per-instance mass reduction), replayed from a captured HIP graph.
+ * The shapes below and the autotuner are those of the single steps.
  * ------------------------------------------------------------------------ */
 typedef struct lbm_batch lbm_batch;
 

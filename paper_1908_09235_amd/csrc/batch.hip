@@ -1,7 +1,11 @@
 // Batched and served forms (include/lbm2p.h, lbm_batch_* and lbm_server_*).
 //
 // A batch holds independent instances, each a full domain (its own
-// geometry, parameters and state) carved out of one device arena.  A step
+// geometry, parameters and state) carved out of one device arena.  A run
+// goes, where that is faster (plan_batch), through launches of several steps
+// over the LDS blocks of every instance, each followed by a reduction that
+// records the masses and advances the instances' step counters; its last step
+// is a single one.  A single step
 // of the batch is three launches on the compute stream: the boundary pass
 // over the link blocks of every instance, the main pass over the tiles of
 // every instance (persistent workgroups over per-XCD tile queues, or one
@@ -51,6 +55,22 @@ struct lbm_batch {
     int tile_w = 256, tile_h = 16, persistent = 1;
     int ring = 3;  // rows of loads per lane of the main pass (2, 3, 4)
     int graph_steps = 32;
+
+    // Several steps per launch (k_block): steps of a launch (0: none, the
+    // batch takes single steps), with the instances' tables in a pool of
+    // their own, so that what fits the arena does not depend on them.
+    int block_steps = 0;
+    bool tuning = false;  // times the single steps' shapes
+    Arena pool;
+    int pool_state = 0;   // 0 not made yet, 1 made, -1 not available
+    BlockArgs* d_block = nullptr;
+    int2* d_btiles = nullptr;
+    BlockArgs* h_block = nullptr;
+    int2* h_btiles = nullptr;
+    int block_cap = 0, btiles_cap = 0;
+    int block_slots = 0;  // slots up to the last instance
+    long long nbtiles = 0;
+    unsigned block_lds = 0;
 
     std::vector<lbm_domain*> inst;        // per slot (nullptr: free)
     std::vector<BState> state;            // host mirror, valid after a sync
@@ -123,17 +143,26 @@ void drop_graph(lbm_batch* b) {
     b->graph = nullptr;
 }
 
+void free_instance(lbm_batch* b, lbm_domain* d) {
+    if (b->pool_state > 0) {
+        domain_drop_blocks(d, &b->pool);
+        if (d->side_mom[1] != d->side_mom[0]) b->pool.release(d->side_mom[1]);
+    }
+    domain_free(d);
+}
+
 void free_batch(lbm_batch* b) {
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     for (lbm_domain* d : b->inst)
-        if (d) domain_free(d);
+        if (d) free_instance(b, d);
     drop_graph(b);
     for (void* p : {(void*)b->d_inst, (void*)b->d_state, (void*)b->d_tiles, (void*)b->d_qnext,
-                    (void*)b->d_qbound, (void*)b->d_lblk, (void*)b->d_nlblk})
+                    (void*)b->d_qbound, (void*)b->d_lblk, (void*)b->d_nlblk, (void*)b->d_block,
+                    (void*)b->d_btiles})
         if (p) (void)hipFree(p);
     for (void* p : {(void*)b->h_inst, (void*)b->h_state, (void*)b->h_tiles, (void*)b->h_lblk,
-                    (void*)b->h_small})
+                    (void*)b->h_small, (void*)b->h_block, (void*)b->h_btiles})
         if (p) (void)hipHostFree(p);
     if (b->ev0) (void)hipEventDestroy(b->ev0);
     if (b->ev1) (void)hipEventDestroy(b->ev1);
@@ -175,7 +204,8 @@ BInst make_inst(lbm_domain* d) {
     I.side_f_bytes = (unsigned)(9 * (d->save_f ? std::max(d->nslots, 1) : 1) * 8);
     I.side_idx = d->side_idx;
     I.psiw = d->psiw;
-    I.side_mom = d->side_mom[0];  // (an instance's two are one)
+    I.side_mom[0] = d->side_mom[0];
+    I.side_mom[1] = d->side_mom[1];
     I.side_f = d->side_f;
     I.partial = d->partial;
     I.mass = d->mass;
@@ -206,6 +236,117 @@ BInst make_inst(lbm_domain* d) {
     return I;
 }
 
+// Steps per launch of k_block for the instances there are (0: single steps):
+// the fewest microseconds a step.  A single step is three launches with few
+// workgroups each, about 28 us and the populations at 5.2 TB/s; a tile of
+// k_block costs less here than in one large lattice (see block_us), whose
+// nodes are all fluid and leave the last cache between launches.  Measured, us
+// a step, single / 2 / 3 / 4 steps per launch:
+//   6 sessile droplets 400 x 200, FP64           41.3 / 18.8 / 17.9 / 21.2
+//   3 droplets of sides 64 to 128, FP64          37.5 /  8.6 /  7.1 /  6.2
+//   12 of sides 64 to 768 (2.8 M nodes), FP64    98.9 / 71.5 / 72.9 / 91.6
+//     FP32 storage, FP64 arithmetic              66.2 / 60.0 / 70.7 / 90.9
+//     FP32 arithmetic                            56.3 / 36.2 / 40.3 / 50.6
+//     FP16 deviations                            52.3 / 41.3 / 46.4 / 58.2
+//   24 of sides 200 to 768 (6.1 M nodes), FP64  202.9 / 145.6 / 147.7 / 190.6
+//     FP32 storage, FP64 arithmetic             116.0 / 124.4 / 144.0 / 188.8
+//     FP32 arithmetic                           109.2 / 83.7 / 84.1 / 105.8
+//     FP16 deviations                            76.0 / 85.7 / 93.5 / 121.6
+// The choice changes only when that gains a tenth, since every instance's
+// tables are made again.
+int plan_batch(lbm_batch* b) {
+    if (b->pool_state < 0 || b->ncu <= 0) return 0;
+    // (the tables are made with waits, which a capture would not take)
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(b->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
+        return 0;
+    double fluid = 0.0;
+    long long tiles[kBlockSteps + 1] = {};
+    const lbm_domain* any = nullptr;
+    for (const lbm_domain* d : b->inst) {
+        if (!d) continue;
+        if (!domain_blockable(d) || d->side_mom[1] == d->side_mom[0]) return 0;
+        any = d;
+        fluid += (double)d->fluid;
+        for (int k = 2; k <= kBlockSteps; ++k) {
+            const long long n = domain_block_tiles(d, k);
+            tiles[k] = n == 0 || tiles[k] < 0 ? -1 : tiles[k] + n;
+        }
+    }
+    if (!any) return 0;
+    double best = 28.0 + 18.0 * (double)any->esize * fluid * 1e-6 / 5.2;
+    int steps = 0;
+    const bool arith64 = b->bd.storage == LBM_STORE_F64 || b->bd.storage == LBM_STORE_F32;
+    const double part = !arith64 ? 0.75 : any->esize == 8 ? 0.92 : 0.78;
+    auto cost = [&](int k) {  // (and the reduction's launch)
+        const long long more = std::max<long long>(tiles[k] - b->ncu, 0);
+        return block_us(any, k, std::min<long long>(tiles[k], b->ncu) + (long long)(part * more),
+                        b->ncu) + 4.7 / k;
+    };
+    for (int k = 2; k <= kBlockSteps; ++k)
+        if (tiles[k] > 0 && tiles[k] < (1 << 24) && cost(k) < best) {
+            best = cost(k);
+            steps = k;
+        }
+    const int now = b->block_steps;
+    if (steps && now && tiles[now] > 0 && cost(now) < 1.1 * best) steps = now;
+    return steps;
+}
+
+// The plan's tables for every instance; single steps if some have none.
+int make_blocks(lbm_batch* b) {
+    b->block_steps = plan_batch(b);
+    b->nbtiles = 0;
+    b->block_lds = 0;
+    if (b->block_steps == 0) return LBM_OK;
+    for (lbm_domain* d : b->inst)
+        if (d && d->block.steps != b->block_steps &&
+            !domain_make_blocks(d, b->block_steps, &b->pool)) {
+            b->block_steps = 0;
+            return LBM_OK;
+        }
+    for (const lbm_domain* d : b->inst)
+        if (d) {
+            b->nbtiles += d->block.ntiles;
+            b->block_lds = std::max(b->block_lds, block_lds(d->block.max_nodes));
+        }
+    if (b->nbtiles > b->btiles_cap) {
+        const int cap = (int)std::max<long long>(b->nbtiles, 2LL * b->btiles_cap);
+        if (b->d_btiles) (void)hipFree(b->d_btiles);
+        if (b->h_btiles) (void)hipHostFree(b->h_btiles);
+        b->d_btiles = nullptr;
+        b->h_btiles = nullptr;
+        b->btiles_cap = 0;
+        if (dmalloc(&b->d_btiles, cap) || hmalloc(&b->h_btiles, cap)) return LBM_ENOMEM;
+        b->btiles_cap = cap;
+    }
+    int n = (int)b->inst.size();
+    while (!b->inst[n - 1]) --n;
+    b->block_slots = n;
+    if (n > b->block_cap) {
+        const int cap = std::min((int)b->inst.size(), std::max(64, 2 * n));
+        if (b->d_block) (void)hipFree(b->d_block);
+        if (b->h_block) (void)hipHostFree(b->h_block);
+        b->d_block = nullptr;
+        b->h_block = nullptr;
+        b->block_cap = 0;
+        if (dmalloc(&b->d_block, cap) || hmalloc(&b->h_block, cap)) return LBM_ENOMEM;
+        b->block_cap = cap;
+    }
+    long long k = 0;
+    for (int i = 0; i < n; ++i) {
+        const lbm_domain* d = b->inst[i];
+        b->h_block[i] = d ? block_args(d) : BlockArgs{};
+        for (int t = 0; d && t < d->block.ntiles; ++t) b->h_btiles[k++] = make_int2(i, t);
+    }
+    if (hipMemcpyAsync(b->d_block, b->h_block, n * sizeof(BlockArgs),
+                       hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+        hipMemcpyAsync(b->d_btiles, b->h_btiles, (size_t)b->nbtiles * sizeof(int2),
+                       hipMemcpyHostToDevice, b->stream) != hipSuccess)
+        return LBM_EDEVICE;
+    return LBM_OK;
+}
+
 // Rebuild and upload the instance, tile and link-block tables.  Only with
 // nothing in flight on the compute stream.
 int rebuild(lbm_batch* b) {
@@ -226,7 +367,7 @@ int rebuild(lbm_batch* b) {
         b->joined[i] = d != nullptr;
         if (!d) {
             b->h_inst[i] = BInst{};
-            b->h_state[i] = BState{0, 0};
+            b->h_state[i] = BState{0, 0, 0, 0};
             continue;
         }
         b->h_inst[i] = make_inst(d);
@@ -251,6 +392,7 @@ int rebuild(lbm_batch* b) {
         hipMemcpyAsync(b->d_nlblk, b->h_small + kQueues + 1, sizeof(int),
                        hipMemcpyHostToDevice, s))
         return LBM_EDEVICE;
+    if ((rc = make_blocks(b))) return rc;
     b->dirty = false;
     return LBM_OK;
 }
@@ -310,7 +452,32 @@ int enqueue(lbm_batch* b, long long n) {
     const BatchLaunch L = launch_of(b);
     const int G = b->graph_steps;
     long long done = 0;
-    if (G > 0 && n >= G) {
+    // n - 1 steps in launches of several, one launch without new steps for
+    // instances that were held back (see block_steps), and a single step
+    if (b->block_steps > 0 && !b->tuning && n > b->block_steps) {
+        BlockBatchLaunch B{};
+        B.args.inst = b->d_block;
+        B.args.state = b->d_state;
+        B.args.tiles = b->d_btiles;
+        B.args.ninst = b->block_slots;
+        B.eos = b->bd.eos;
+        B.storage = b->bd.storage;
+        B.ntiles = (int)b->nbtiles;
+        B.red_grid = L.red_grid;
+        B.lds = b->block_lds;
+        B.stream = b->stream;
+        for (bool more = true; more;) {
+            const int k = (int)std::min<long long>(n - 1 - done, b->block_steps);
+            more = k > 0;
+            B.args.steps = k;
+            if (b->bd.storage == LBM_STORE_F64) launch_block_batch_f64(B);
+            else launch_block_batch_f32(B);
+            done += k;
+        }
+        launch_step(b, L);
+        done = n;
+    }
+    if (G > 0 && n - done >= G) {
         const int key[8] = {b->tile_w, b->persistent, L.main_grid, G, L.save_f ? 1 : 0,
                             L.bnd_grid, L.red_grid, L.ring};
         if (b->graph && std::memcmp(key, b->graph_key, sizeof key) != 0) drop_graph(b);
@@ -354,7 +521,7 @@ int sync_batch(lbm_batch* b) {
         lbm_domain* d = b->inst[i];
         if (!d) continue;
         d->t = b->state[i].t;
-        d->cur = (int)(d->t & 1);
+        d->cur = b->state[i].cur;
         d->pending = false;
         d->pending_t = d->t;
     }
@@ -380,8 +547,18 @@ int batch_add(lbm_batch* b, const lbm_desc* desc, long long steps, int* slot) {
     // A reused slot may still be listed in the device tables, with the
     // stopped state of its previous instance, until the next rebuild: the
     // launches skip it, and its device state is not read back meanwhile.
+    // moments of its own for each buffer, from the pool of the block tables
+    if (b->pool_state == 0) {
+        const size_t want = std::min<size_t>(
+            std::max<size_t>((size_t)b->bd.arena_bytes / 8, 4 << 20), 256 << 20);
+        b->pool_state = b->pool.init(want) == LBM_OK ? 1 : -1;
+        if (b->pool_state < 0) (void)hipGetLastError();
+    }
+    if (b->pool_state > 0 && domain_blockable(d))
+        if (void* p = b->pool.alloc((size_t)3 * std::max(d->nslots, 1) * 8))
+            d->side_mom[1] = static_cast<double*>(p);
     b->inst[s] = d;
-    b->state[s] = BState{0, steps};
+    b->state[s] = BState{0, steps, 0, 0};
     b->joined[s] = 0;
     b->dirty = true;
     *slot = s;
@@ -395,9 +572,9 @@ int batch_remove(lbm_batch* b, int slot) {
         int rc = sync_batch(b);
         if (rc) return rc;
     }
-    domain_free(d);
+    free_instance(b, d);
     b->inst[slot] = nullptr;
-    b->state[slot] = BState{0, 0};
+    b->state[slot] = BState{0, 0, 0, 0};
     b->dirty = true;
     return LBM_OK;
 }
@@ -472,7 +649,7 @@ int lbm_batch_create(const lbm_batch_desc* bd, lbm_batch** out) {
         return LBM_EDEVICE;
     }
     b->inst.assign(n, nullptr);
-    b->state.assign(n, BState{0, 0});
+    b->state.assign(n, BState{0, 0, 0, 0});
     b->joined.assign(n, 0);
     *out = b;
     return LBM_OK;
@@ -558,6 +735,7 @@ int lbm_batch_tune(lbm_batch* b, int64_t steps_per_trial, int32_t out[5]) {
     int bw = b->tile_w, bh = b->tile_h, bp = b->persistent, br = b->ring;
     const int G = b->graph_steps;
     b->graph_steps = 0;  // time plain launches (no capture per candidate)
+    b->tuning = true;    // of single steps
     for (int ri = 0; ri < nring && !rc; ++ri)
         for (int p = 0; p <= 1 && !rc; ++p)
             for (int wi = 0; wi < 3 && !rc; ++wi)
@@ -588,6 +766,7 @@ int lbm_batch_tune(lbm_batch* b, int64_t steps_per_trial, int32_t out[5]) {
                 }
             }
     b->graph_steps = G;
+    b->tuning = false;
     b->tile_w = bw;
     b->tile_h = bh;
     b->persistent = bp;
@@ -713,7 +892,7 @@ int lbm_server_result(lbm_server* s, int64_t id, double* rho, double* ux, double
     lbm_domain* d = s->b->inst[slot];
     // read-out on the setup stream; the compute stream skips this instance
     d->t = s->b->state[slot].t;
-    d->cur = (int)(d->t & 1);
+    d->cur = s->b->state[slot].cur;
     d->pending = false;
     int rc = LBM_OK;
     if (rho || ux || uy) rc = lbm_moments(d, rho, ux, uy);

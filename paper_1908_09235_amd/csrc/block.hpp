@@ -84,36 +84,35 @@ __host__ __device__ __forceinline__ int2 block_place(int tile, int nstrips, int 
 }
 
 struct BlockArgs {
-    const void* __restrict__ src;          // f*(t)
-    void* __restrict__ dst;                // f*(t + steps)
-    const uint8_t* __restrict__ flags;
-    const float* __restrict__ psiw;        // FP16 storage: psi_w of solid nodes
-    const double* __restrict__ mom_in;     // side moments of t
-    double* __restrict__ mom_out;          // ... and of t + steps
-    MassPart* __restrict__ partial;        // [step][tile]
-    long long partial_stride;
-    const BlockTile* __restrict__ tiles;
-    const BlockLink* __restrict__ links;
-    const BlockNode* __restrict__ nodes;
-    const double* __restrict__ lc;         // link tables (see BndArgs)
-    const double* __restrict__ luw;
-    unsigned long long* __restrict__ negrest;
-    unsigned long long* __restrict__ degen;
+    void* f[2];                            // f[cur]: f*(t); f*(t + steps) goes to the other
+    double* mom[2];                        // side moments of the times of f[0], f[1]
+    const uint8_t* flags;
+    const float* psiw;                     // FP16 storage: psi_w of solid nodes
+    MassPart* partial;                     // [step][tile]
+    const BlockTile* tiles;
+    const BlockLink* links;
+    const BlockNode* nodes;
+    const double* lc;                      // link tables (see BndArgs)
+    const double* luw;
+    unsigned long long* negrest;
+    unsigned long long* degen;
     int fix, moving;                       // moving: some wall has a velocity
     int chi;                               // the rule is of the form of Eq. (7)
     int max_len;                           // links of a node, at most
     int nx, ny, pitch;
     long long plane;
-    int steps, halo, pull;                 // pull: margin of a step's pull
+    int halo, pull;                        // pull: margin of a step's pull
     int nstrips, ntiles, nsegs;
     int max_nodes;                         // moment records of LDS
     unsigned mom_bytes, link_bytes, node_bytes;
     int open_x;
     double inlet_u;
     MassUnit mass;
-    // reduction of the previous launch's masses (last workgroup)
-    MassPass prev;
-    int do_reduce;
+    double* hist;                          // (batches: see BInst)
+    long long cap;
+    long long* unstable;
+    Phys<double> ph64;
+    Phys<float> ph32;
 };
 
 // The value of the next lane (whole-wavefront shift; the last lane gets 0).
@@ -124,19 +123,10 @@ __device__ __forceinline__ double next_lane(double v) {
     return __builtin_bit_cast(double, uint2_t{(unsigned)lo, (unsigned)hi});
 }
 
-// The kernel's arguments as they lie in its argument segment.
 template <typename R>
-struct BlockKernarg {
-    BlockArgs a;
-    Phys<R> ph;
-};
-template <typename R>
-__device__ __forceinline__ const BlockKernarg<R>* kernarg() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return (const BlockKernarg<R>*)__builtin_amdgcn_kernarg_segment_ptr();
-#else
-    return nullptr;
-#endif
+__device__ __forceinline__ Phys<R> block_phys(const LBM_CONST_AS BlockArgs& a) {
+    if constexpr (sizeof(R) == 8) return a.ph64;
+    else return a.ph32;
 }
 
 // Wavefronts per SIMD: two workgroups of 512 lanes on a CU (FP64 populations
@@ -146,10 +136,10 @@ constexpr int block_waves(int nt) {
     return sizeof(R) == 4 && nt == kBlockThreads ? 6 : 4;
 }
 
+// `steps` steps of tile `tile` of the domain described at ka (uniform, in
+// memory that no launch writes), whose f*(t) lies in f[cur].
 template <typename S, typename R, int EOS, int DEV, int RW, int RH, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(block_waves<R>(NT)))) void
-k_block(
-    BlockArgs a, Phys<R> ph0) {
+__device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int steps, int tile) {
     static_assert(DEV == 0 || DEV == 1, "per-node references are not blocked");
     constexpr int NN = RW * RH, NPT = NN / NT, NW = NT / 64;
     static_assert(NN % NT == 0 && NT % 64 == 0, "every thread has as many nodes");
@@ -160,15 +150,11 @@ k_block(
     __shared__ unsigned long long mq[kBlockSteps][kBlockBins], mfine[kBlockSteps][kBlockBins];
     __shared__ double mbig[kBlockSteps][NW];
     extern __shared__ double dyn[];
+    const LBM_CONST_AS BlockArgs& a = *ro(args);
     double* const mom = dyn;                        // [record][3]: rho, u_x, u_y
     double* const leak = dyn + 3 * a.max_nodes;     // scheme A: [record]
 
     const int t = threadIdx.x;
-    if ((int)blockIdx.x == (int)gridDim.x - 1) {
-        if (a.do_reduce) reduce_pass(a.prev);
-        return;
-    }
-    const int tile = xcd_tile(blockIdx.x, a.ntiles);
     const int2 place = block_place(tile, a.nstrips, a.nsegs);
     const int strip = place.x, seg = place.y;
     auto share = [](int k, int n, int parts) {
@@ -177,13 +163,13 @@ k_block(
     const int x0 = share(strip, a.nx, a.nstrips), y0 = share(seg, a.ny, a.nsegs);
     const int ncols = share(strip + 1, a.nx, a.nstrips) - x0;
     const int nrows = share(seg + 1, a.ny, a.nsegs) - y0;
-    const int halo = a.halo, steps = a.steps, pull = a.pull;
+    const int halo = a.halo, pull = a.pull;
     const int fix = a.fix, moving = a.moving, max_len = a.max_len;
     const int open_x = a.open_x, chi = a.chi;
     const int reach = pull + (EOS == EOS_NONE ? 0 : 1);
     const unsigned pitch = (unsigned)a.pitch;
     const unsigned pb = (unsigned)(a.plane * ES);
-    const rsrc_t rs = make_rsrc(a.src, 9u * pb);
+    const rsrc_t rs = make_rsrc(cur ? a.f[1] : a.f[0], 9u * pb);
     const rsrc_t rfl = make_rsrc(a.flags, pitch * (unsigned)a.ny);
     const rsrc_t rpw = make_rsrc(a.psiw, ES == 2 ? pitch * (unsigned)a.ny * 4u : 0u);
     // local coordinates of the thread's node j, and its place in the lattice
@@ -209,7 +195,7 @@ k_block(
     // buffer, which yields 0, so each wait leaves the later loads in flight.
     const BlockTile bt = ro(a.tiles)[tile];
     const rsrc_t rli = make_rsrc(a.links, a.link_bytes), rno = make_rsrc(a.nodes, a.node_bytes);
-    const rsrc_t rmo = make_rsrc(a.mom_in, a.mom_bytes);
+    const rsrc_t rmo = make_rsrc(cur ? a.mom[1] : a.mom[0], a.mom_bytes);
     uint4_t l0, l1;
     S f0[NPT];
     // per node, 16 bits: 1 solid, 2 own, 4 scheme A's; (moment record + 1) << 3
@@ -286,14 +272,13 @@ k_block(
         // The arguments and the thread's place are read anew in every step:
         // kept over the loop, they and what is derived from them would take
         // more registers than there are.
-        const BlockKernarg<R>* ka = kernarg<R>();
+        const BlockArgs* ka = args;
         int t = threadIdx.x;
         asm volatile("" : "+s"(ka));
         asm volatile("" : "+v"(t), "+v"(l0), "+v"(l1), "+v"(info));
         const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-        const LBM_CONST_AS BlockKernarg<R>& K = *ro(ka);
-        const auto& a = K.a;
-        const Phys<R> ph = K.ph;
+        const LBM_CONST_AS BlockArgs& a = *ro(ka);
+        const Phys<R> ph = block_phys<R>(a);
         // ---- walls
         if (bt.chunks > 0) {
             if (wave < bt.chunks) {
@@ -441,7 +426,9 @@ k_block(
         const bool last = s == steps;
         constexpr bool SPLIT = sizeof(R) == 8 || DEV != 0;
         MassSum<SPLIT> msum;
-        const MassUnit mass = a.mass;
+        MassUnit mass;
+        mass.magic = a.mass.magic;
+        mass.unit = a.mass.unit;
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
             const int n = t + j * NT, lx = lx_at(t, j), ly = ly_at(t, j);
@@ -469,7 +456,7 @@ k_block(
                 R dh[9];
                 collide<R>(fc, rho, drho, ux, uy, Fx, Fy, ph, dh);
                 if (last) {
-                    const rsrc_t rd = make_rsrc(a.dst, 9u * pb);
+                    const rsrc_t rd = make_rsrc(cur ? a.f[0] : a.f[1], 9u * pb);
                     const unsigned vo = at(t, j, a.nx, a.ny) * ES;
 #pragma unroll
                     for (int q = 0; q < 9; ++q) bstore(S(fc[q] + dh[q]), rd, vo, q * pb);
@@ -506,9 +493,10 @@ k_block(
     // ---- moments of t + steps and the masses
     if (t < bt.nodes) {
         const BlockNode n = a.nodes[bt.node0 + t];
+        double* const out = cur ? a.mom[0] : a.mom[1];
         if (n.own) {
 #pragma unroll
-            for (int k = 0; k < 3; ++k) a.mom_out[3 * n.slot + k] = mom[3 * t + k];
+            for (int k = 0; k < 3; ++k) out[3 * n.slot + k] = mom[3 * t + k];
         }
     }
     if (t < steps) {
@@ -519,7 +507,91 @@ k_block(
         }
         double big = 0.0;
         for (int w = 0; w < NW; ++w) big += mbig[t][w];
-        a.partial[t * a.partial_stride + tile] = MassPart{q & 0xffffffffll, q >> 32, fine, big};
+        a.partial[(long long)t * a.ntiles + tile] = MassPart{q & 0xffffffffll, q >> 32, fine, big};
+    }
+}
+
+// One domain; the last workgroup reduces the previous launch's masses.
+struct BlockRun {
+    int cur, steps, do_reduce;
+    MassPass prev;
+};
+struct BlockKernarg {
+    BlockArgs a;
+    BlockRun r;
+};
+template <typename S, typename R, int EOS, int DEV, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(block_waves<R>(NT)))) void
+k_block(BlockKernarg k) {
+    if ((int)blockIdx.x == (int)gridDim.x - 1) {
+        if (k.r.do_reduce) reduce_pass(k.r.prev);
+        return;
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    // (the arguments where they lie, to be read again in every step)
+    const BlockArgs* args = (const BlockArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+#else
+    const BlockArgs* args = &k.a;
+#endif
+    block_tile<S, R, EOS, DEV, kBlockW, kBlockH, NT>(args, k.r.cur, k.r.steps,
+                                                     xcd_tile(blockIdx.x, k.a.ntiles));
+}
+
+// ---------------------------------------------------------------- batches
+// The instances of a batch advance together, up to `steps` steps a launch.
+// An instance leaves its last step, and a step that turned out non-finite, to
+// single steps, so that it ends as they would leave it: a launch that meets
+// a non-finite mass in step j is dropped for that instance (its f*(t) is
+// still there), the next one makes j - 1 steps, and single steps go on.
+__device__ __forceinline__ int block_steps(long long remaining, int hold, int steps) {
+    if (remaining <= 0 || hold < 0) return 0;
+    if (hold > 0) return hold;
+    return remaining - 1 < steps ? (int)(remaining - 1) : steps;
+}
+
+struct BlockBatch {
+    const BlockArgs* __restrict__ inst;  // per slot
+    BState* __restrict__ state;
+    const int2* __restrict__ tiles;      // (instance, tile)
+    int ninst, steps;
+};
+
+template <typename S, typename R, int EOS, int DEV>
+__global__ __launch_bounds__(kBlockThreads)
+    __attribute__((amdgpu_waves_per_eu(block_waves<R>(kBlockThreads)))) void k_block_batch(
+        BlockBatch b) {
+    const int2 te = ro(b.tiles)[xcd_tile(blockIdx.x, gridDim.x)];
+    const BState st = ro<BState>(b.state)[te.x];
+    const int n = block_steps(st.remaining, st.hold, b.steps);
+    if (n <= 0) return;
+    block_tile<S, R, EOS, DEV, kBlockW, kBlockH, kBlockThreads>(b.inst + te.x, st.cur, n, te.y);
+}
+
+// Per instance: the masses of the launch and the state it leaves.
+template <int Unused = 0>
+__global__ __launch_bounds__(256) void k_block_reduce(BlockBatch b) {
+    __shared__ double m[kBlockSteps];
+    for (int i = blockIdx.x; i < b.ninst; i += gridDim.x) {
+        BState* st = b.state + i;
+        const int n = block_steps(st->remaining, st->hold, b.steps);
+        if (n <= 0) continue;
+        const auto& I = ro(b.inst)[i];
+        sum_masses(I.partial, I.ntiles, n, I.ntiles, I.mass.unit,
+                   [&](int s, double v) { m[s] = v; });
+        if (threadIdx.x == 0) {
+            int bad = 0;
+            while (bad < n && isfinite(m[bad])) ++bad;
+            if (bad == n) {
+                for (int s = 0; s < n; ++s) I.hist[(st->t + 1 + s) % I.cap] = m[s];
+                st->t += n;
+                st->remaining -= n;
+                st->cur ^= 1;
+                if (st->hold > 0) st->hold = -1;
+            } else {
+                st->hold = bad > 0 ? bad : -1;
+            }
+        }
+        __syncthreads();
     }
 }
 

@@ -53,6 +53,12 @@ struct BlockPlan {
     int set = 0;                                // the one written last
 };
 
+// Host copies of the link tables that k_block's tables are made from.
+struct LinkTables {
+    std::vector<int> node, meta, slotb, slotf;
+    std::vector<double> c;
+};
+
 }  // namespace lbm
 
 struct lbm_domain {
@@ -104,6 +110,7 @@ struct lbm_domain {
     int pending_steps = 0;       // steps of the last pass whose masses are pending
     bool pending_block = false;  // it was a launch of k_block
     lbm::BlockPlan block;
+    lbm::LinkTables links;       // instances of a batch: kept for new plans
     // After a two-step pass f*(t - 1) is not in memory: the buffer that
     // held f*(t - 2) still does, with the ghosts of step t - 1, and the
     // moments at t and the wall force of the last step are read from a
@@ -148,6 +155,36 @@ void domain_free(lbm_domain* d);
 // most partial_cap tiles); the next launch uses it.
 int domain_set_tiles(lbm_domain* d, int tile_w, int tile_h);
 Ctx domain_ctx(lbm_domain* d);
+
+// k_block (see block.hpp).  Zhao-Yong needs the pre-collision populations of
+// the step before, and the FP16 per-node form a second plane: both stay with
+// single steps.
+bool domain_blockable(const lbm_domain* d);
+// Tiles of a launch of `steps` steps (0: its halos leave none).
+long long domain_block_tiles(const lbm_domain* d, int steps);
+// The tables of `steps` steps per launch for an instance of a batch, in memory
+// of `pool` (false if it has none left or the tables do not fit a tile; the
+// instance has no plan then).  Waits for the instance's stream.
+bool domain_make_blocks(lbm_domain* d, int steps, Arena* pool);
+void domain_drop_blocks(lbm_domain* d, Arena* pool);
+BlockArgs block_args(const lbm_domain* d);
+
+// Estimated time of a step in us: single steps (boundary and main launch), and
+// launches of k_block with `steps` steps on `tiles` tiles.  Fitted to measured
+// steps of droplets (64^2 to 2048^2) and of the static channel; what matters
+// is where the curves cross.
+//   single: two launches and the populations at 4.6 TB/s (FP16 at 3.7);
+//     measured in FP64 / FP32 / FP16 storage: 13.3 / 12.2 / 12 at 400^2,
+//     31.4 / 24.7 / 20 at 1024^2, 132 / 75 / 48 at 2048^2.
+//   k_block: 6.6 us a launch and 3.3 a step while every tile has a CU of its
+//     own, then a cost per further tile, of which the two-phase step, FP64
+//     arithmetic and the halos (a step more shrinks the tiles) are the parts.
+//     Measured for the droplet in FP64 storage: 6 steps at 128^2 4.4 a step,
+//     3 at 400^2 7.6, 2 at 1024^2 26.3, 2 at 2048^2 96; in FP32 storage with
+//     FP64 arithmetic 18.2 at 800^2, 24.9 at 1024^2, 80 at 2048^2 (arithmetic
+//     of the halos: single steps are faster from 1024^2 on).
+double single_us(size_t esize, double fluid);
+double block_us(const lbm_domain* d, int steps, long long tiles, int ncu);
 // The buffer the moments at the current time are pulled from: f*(t - 1)
 // with the ghosts of step t (after a two-step pass, rebuilt by a replay of
 // step t - 1 into the domain's replay buffer; also forms the wall force of

@@ -1000,11 +1000,11 @@ __global__ void k_psi_wall(S* __restrict__ b0, S* __restrict__ b1, float* __rest
 
 // What the kernels read about one instance.
 struct BInst {
-    void* f[2];  // state buffers; f[t & 1] holds f*(t)
+    void* f[2];  // state buffers; f[BState::cur] holds f*(t)
     const uint8_t* flags;
     const int* side_idx;
     const float* psiw;
-    double* side_mom;
+    double* side_mom[2];  // of the times of f[0], f[1] (or one for both)
     double* side_f;
     MassPart* partial;  // one mass partial per tile
     MassUnit mass;
@@ -1028,6 +1028,8 @@ struct BInst {
 struct BState {
     long long t;
     long long remaining;
+    int cur;   // f[cur] holds f*(t)
+    int hold;  // see block_steps
 };
 
 // Ints between two queue heads of the persistent form: each head on a
@@ -1050,15 +1052,14 @@ struct BatchArgs {
 };
 
 template <typename S, typename I_t>
-__device__ __forceinline__ MainArgs<S> inst_main_args(const I_t& I, long long t, int tile_h) {
+__device__ __forceinline__ MainArgs<S> inst_main_args(const I_t& I, int c, int tile_h) {
     MainArgs<S> a;
-    const int c = int(t & 1);
     a.src = static_cast<const S*>(I.f[c]);
     a.dst = static_cast<S*>(I.f[c ^ 1]);
     a.flags = I.flags;
     a.side_idx = I.side_idx;
     a.psiw = I.psiw;
-    a.side_mom = I.side_mom;
+    a.side_mom = I.side_mom[c ^ 1];
     a.side_f = I.side_f;
     a.partial = I.partial;
     a.mass.magic = I.mass.magic;
@@ -1085,7 +1086,7 @@ __device__ __forceinline__ void batch_tile(const BatchArgs& b, int g) {
     if (st.remaining <= 0) return;
     const auto& I = ro(b.inst)[te.x];
     const Phys<double> ph = I.ph;
-    main_tile<S, R, EOS, false, DEV, SAVEF, RING>(inst_main_args<S>(I, st.t, b.tile_h),
+    main_tile<S, R, EOS, false, DEV, SAVEF, RING>(inst_main_args<S>(I, st.cur, b.tile_h),
                                                   phys_as<R>(ph), te.y);
 }
 
@@ -1147,7 +1148,7 @@ __global__ __launch_bounds__(256) void k_boundary_batch(BatchArgs b) {
         a.lslotf = I.lslotf;
         a.lc = I.lc;
         a.luw = I.luw;
-        a.side_mom = I.side_mom;
+        a.side_mom = I.side_mom[st.cur];
         a.side_f = I.side_f;
         a.plane = I.plane;
         a.rref = I.rref;
@@ -1162,7 +1163,7 @@ __global__ __launch_bounds__(256) void k_boundary_batch(BatchArgs b) {
         a.nx = a.ny = a.pitch = 0;
         a.inlet_u = 0.0;
         __syncthreads();  // the previous block is done with the LDS
-        boundary_block<S, DEV>(static_cast<S*>(I.f[st.t & 1]), a, e.y);
+        boundary_block<S, DEV>(static_cast<S*>(I.f[st.cur]), a, e.y);
     }
 }
 
@@ -1184,6 +1185,8 @@ __global__ __launch_bounds__(256) void k_reduce_batch(BatchArgs b) {
         });
         if (threadIdx.x == 0) {
             st->t = t1;
+            st->cur ^= 1;
+            st->hold = 0;
             st->remaining = *I.unstable >= 0 ? 0 : rem - 1;
         }
     }

@@ -54,8 +54,8 @@ void launch_main_f32(const Ctx& c, const void* src, void* dst, bool moments);
 void launch_main2_f32(const Ctx& c, const void* src, void* dst);
 // several steps per launch (see block.hpp): 1024 lanes per tile (wide) or
 // 512; lds: bytes of dynamic LDS
-void launch_block_f64(const Ctx& c, const BlockArgs& a, bool wide, unsigned lds);
-void launch_block_f32(const Ctx& c, const BlockArgs& a, bool wide, unsigned lds);
+void launch_block_f64(const Ctx& c, const BlockKernarg& k, bool wide, unsigned lds);
+void launch_block_f32(const Ctx& c, const BlockKernarg& k, bool wide, unsigned lds);
 // one boundary pass on cur
 void launch_boundary_f64(const Ctx& c, void* cur, const BndArgs& b, int nblocks);
 void launch_boundary_f32(const Ctx& c, void* cur, const BndArgs& b, int nblocks);
@@ -85,6 +85,16 @@ struct BatchLaunch {
 void launch_batch_f64(const BatchLaunch& L);
 void launch_batch_f32(const BatchLaunch& L);
 void launch_batch_reduce(const BatchLaunch& L);
+// several steps of every instance, then their masses and states
+struct BlockBatchLaunch {
+    BlockBatch args;
+    int eos, storage;
+    int ntiles, red_grid;
+    unsigned lds;
+    hipStream_t stream;
+};
+void launch_block_batch_f64(const BlockBatchLaunch& L);
+void launch_block_batch_f32(const BlockBatchLaunch& L);
 // resident workgroups per CU of the batched main kernel
 int batch_occupancy_f64(int eos, int storage, int tile_w, bool save_f, int ring);
 int batch_occupancy_f32(int eos, int storage, int tile_w, bool save_f, int ring);

@@ -24,6 +24,90 @@ constexpr int kMinTileH2 = 4;
 
 }  // namespace
 
+namespace lbm {
+
+// Nodes a pull reaches (x_ff of the quadratic interpolation lies two away),
+// and a whole step of k_block.
+static int block_pull(const lbm_domain* d) { return d->rule == LBM_RULE_IBB_QUADRATIC ? 2 : 1; }
+static int block_reach(const lbm_domain* d) {
+    return block_pull(d) + (d->eos == EOS_NONE ? 0 : 1);
+}
+
+bool domain_blockable(const lbm_domain* d) {
+    return d->storage != LBM_STORE_F16NODE && d->rule != LBM_RULE_ZHAO_YONG;
+}
+
+long long domain_block_tiles(const lbm_domain* d, int steps) {
+    const int halo = steps * block_reach(d);
+    const int ow = kBlockW - 2 * halo, oh = kBlockH - 2 * halo;
+    if (ow < 4 || oh < 4) return 0;
+    return (long long)((d->nx + ow - 1) / ow) * ((d->ny + oh - 1) / oh);
+}
+
+double single_us(size_t esize, double fluid) {
+    return 8.0 + 18.0 * (double)esize * fluid * 1e-6 / (esize == 2 ? 3.7 : 4.6);
+}
+
+double block_us(const lbm_domain* d, int steps, long long tiles, int ncu) {
+    const bool two_phase = d->eos != EOS_NONE;
+    const bool arith64 = d->storage == LBM_STORE_F64 || d->storage == LBM_STORE_F32;
+    double us = 6.6 + 3.3 * steps;
+    if (tiles > ncu) {
+        const double per = two_phase ? (arith64 ? 0.0175 + 0.0037 * steps : 0.0105 + 0.0031 * steps)
+                                     : (d->esize == 8 ? 0.0245 + 0.0023 * steps
+                                                      : 0.0145 + 0.0040 * steps);
+        us += 5.0 + per * (double)(tiles - ncu);
+    }
+    return us / steps;
+}
+
+BlockArgs block_args(const lbm_domain* d) {
+    const BlockPlan& p = d->block;
+    BlockArgs a{};
+    for (int k = 0; k < 2; ++k) {
+        a.f[k] = d->f[k];
+        a.mom[k] = d->side_mom[k];
+    }
+    a.flags = d->flags;
+    a.psiw = d->psiw;
+    a.partial = p.partial[p.set];
+    a.tiles = p.tiles;
+    a.links = p.links;
+    a.nodes = p.nodes;
+    a.lc = d->lc;
+    a.luw = d->luw;
+    a.negrest = d->negrest;
+    a.degen = d->degen;
+    a.fix = d->fix;
+    a.moving = p.moving ? 1 : 0;
+    a.chi = d->rule == LBM_RULE_HALFWAY || d->rule == LBM_RULE_FH || d->rule == LBM_RULE_MLS;
+    a.max_len = p.max_len;
+    a.nx = d->nx;
+    a.ny = d->ny;
+    a.pitch = d->pitch;
+    a.plane = d->plane;
+    a.halo = p.halo;
+    a.pull = p.pull;
+    a.nstrips = p.nstrips;
+    a.nsegs = p.nsegs;
+    a.ntiles = p.ntiles;
+    a.max_nodes = p.max_nodes;
+    a.mom_bytes = (unsigned)(3 * std::max(d->nslots, 1) * 8);
+    a.link_bytes = p.link_bytes;
+    a.node_bytes = p.node_bytes;
+    a.open_x = d->open_x;
+    a.inlet_u = d->inlet_u;
+    a.mass = d->mass;
+    a.hist = d->hist;
+    a.cap = d->cap;
+    a.unstable = d->unstable;
+    a.ph64 = d->ph64;
+    a.ph32 = phys_as<float>(d->ph64);
+    return a;
+}
+
+}  // namespace lbm
+
 namespace {
 
 int dev_alloc(lbm_domain* d, void** p, size_t bytes) {
@@ -354,49 +438,16 @@ bool uses_blocks(const lbm_domain* d) {
 // previous one.
 void launch_block(lbm_domain* d, int k) {
     BlockPlan& p = d->block;
-    BlockArgs a{};
-    a.src = d->f[d->cur];
-    a.dst = d->f[d->cur ^ 1];
-    a.flags = d->flags;
-    a.psiw = d->psiw;
-    a.mom_in = d->side_mom[d->cur];
-    a.mom_out = d->side_mom[d->cur ^ 1];
-    a.prev = mass_pass(d);
-    a.do_reduce = d->pending ? 1 : 0;
+    BlockKernarg arg{};
+    arg.r.cur = d->cur;
+    arg.r.steps = k;
+    arg.r.prev = mass_pass(d);
+    arg.r.do_reduce = d->pending ? 1 : 0;
     p.set ^= 1;
-    a.partial = p.partial[p.set];
-    a.partial_stride = p.ntiles;
-    a.tiles = p.tiles;
-    a.links = p.links;
-    a.nodes = p.nodes;
-    a.lc = d->lc;
-    a.luw = d->luw;
-    a.negrest = d->negrest;
-    a.degen = d->degen;
-    a.fix = d->fix;
-    a.moving = p.moving ? 1 : 0;
-    a.chi = d->rule == LBM_RULE_HALFWAY || d->rule == LBM_RULE_FH || d->rule == LBM_RULE_MLS;
-    a.max_len = p.max_len;
-    a.nx = d->nx;
-    a.ny = d->ny;
-    a.pitch = d->pitch;
-    a.plane = d->plane;
-    a.steps = k;
-    a.halo = p.halo;
-    a.pull = p.pull;
-    a.nstrips = p.nstrips;
-    a.nsegs = p.nsegs;
-    a.ntiles = p.ntiles;
-    a.max_nodes = p.max_nodes;
-    a.open_x = d->open_x;
-    a.inlet_u = d->inlet_u;
-    a.mass = d->mass;
-    a.mom_bytes = (unsigned)(3 * std::max(d->nslots, 1) * 8);
-    a.link_bytes = p.link_bytes;
-    a.node_bytes = p.node_bytes;
+    arg.a = block_args(d);
     const unsigned lds = block_lds(p.max_nodes);
-    if (d->storage == LBM_STORE_F64) launch_block_f64(ctx(d), a, p.wide, lds);
-    else launch_block_f32(ctx(d), a, p.wide, lds);
+    if (d->storage == LBM_STORE_F64) launch_block_f64(ctx(d), arg, p.wide, lds);
+    else launch_block_f32(ctx(d), arg, p.wide, lds);
     d->cur ^= 1;
     d->t += k;
     d->pending = true;
@@ -596,11 +647,6 @@ struct LinkRec {
     int src;   // index in the descriptor
 };
 
-// Nodes a pull reaches (x_ff of the quadratic interpolation lies two away),
-// and a whole step of k_block.
-int block_pull(const lbm_domain* d) { return d->rule == LBM_RULE_IBB_QUADRATIC ? 2 : 1; }
-int block_reach(const lbm_domain* d) { return block_pull(d) + (d->eos == EOS_NONE ? 0 : 1); }
-
 // Tables of k_block for `steps` steps per launch: per tile the cut links
 // whose fluid node its region pulls, grouped by node in chunks of 64, and the
 // nodes whose moments they read.  False if a tile holds more than a workgroup
@@ -611,10 +657,24 @@ struct BlockTables {
     std::vector<BlockLink> links;
     std::vector<BlockNode> nodes;
 };
-bool block_tables(const lbm_domain* d, int steps, const std::vector<int>& lnode,
-                  const std::vector<int>& lmeta, const std::vector<int>& lslotb,
-                  const std::vector<int>& lslotf, const std::vector<double>& lc,
-                  BlockTables& b) {
+// What the plan says of them.
+void block_plan(lbm_domain* d, const BlockTables& b) {
+    BlockPlan& p = d->block;
+    p.halo = b.halo;
+    p.pull = b.pull;
+    p.nstrips = b.nstrips;
+    p.nsegs = b.nsegs;
+    p.ntiles = b.nstrips * b.nsegs;
+    p.max_nodes = b.max_nodes;
+    p.max_len = b.max_len;
+    p.link_bytes = (unsigned)(b.links.size() * sizeof(BlockLink));
+    p.node_bytes = (unsigned)(b.nodes.size() * sizeof(BlockNode));
+    p.steps = b.steps;
+}
+bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTables& b) {
+    const std::vector<int>&lnode = lt.node, &lmeta = lt.meta, &lslotb = lt.slotb,
+                    &lslotf = lt.slotf;
+    const std::vector<double>& lc = lt.c;
     b = BlockTables{};
     b.steps = steps;
     b.pull = block_pull(d);
@@ -726,57 +786,19 @@ bool block_tables(const lbm_domain* d, int steps, const std::vector<int>& lnode,
     return true;
 }
 
-// Estimated time of a step in us: single steps (boundary and main launch), and
-// launches of k_block with `steps` steps on `tiles` tiles.  Fitted to measured
-// steps of droplets (64^2 to 2048^2) and of the static channel; what matters
-// is where the curves cross.
-//   single: two launches and the populations at 4.6 TB/s (FP16 at 3.7);
-//     measured in FP64 / FP32 / FP16 storage: 13.3 / 12.2 / 12 at 400^2,
-//     31.4 / 24.7 / 20 at 1024^2, 132 / 75 / 48 at 2048^2.
-//   k_block: 6.6 us a launch and 3.3 a step while every tile has a CU of its
-//     own, then a cost per further tile, of which the two-phase step, FP64
-//     arithmetic and the halos (a step more shrinks the tiles) are the parts.
-//     Measured for the droplet in FP64 storage: 6 steps at 128^2 4.4 a step,
-//     3 at 400^2 7.6, 2 at 1024^2 26.3, 2 at 2048^2 96; in FP32 storage with
-//     FP64 arithmetic 18.2 at 800^2, 24.9 at 1024^2, 80 at 2048^2 (arithmetic
-//     of the halos: single steps are faster from 1024^2 on).
-double single_us(const lbm_domain* d) {
-    const double mb = 18.0 * (double)d->esize * (double)d->fluid * 1e-6;
-    return 8.0 + mb / (d->esize == 2 ? 3.7 : 4.6);
-}
-double block_us(const lbm_domain* d, int steps, long long tiles, int ncu) {
-    const bool two_phase = d->eos != EOS_NONE;
-    const bool arith64 = d->storage == LBM_STORE_F64 || d->storage == LBM_STORE_F32;
-    double us = 6.6 + 3.3 * steps;
-    if (tiles > ncu) {
-        const double per = two_phase ? (arith64 ? 0.0175 + 0.0037 * steps : 0.0105 + 0.0031 * steps)
-                                     : (d->esize == 8 ? 0.0245 + 0.0023 * steps
-                                                      : 0.0145 + 0.0040 * steps);
-        us += 5.0 + per * (double)(tiles - ncu);
-    }
-    return us / steps;
-}
-
 // Whether and how the domain's runs go through k_block: the number of steps
 // per launch with the least estimated time, if that is below single steps'.
-// (Zhao-Yong needs the pre-collision populations of the step before, and the
-// FP16 per-node form a second plane; both stay with single steps.)
-int plan_blocks(lbm_domain* d, const std::vector<int>& lnode, const std::vector<int>& lmeta,
-                const std::vector<int>& lslotb, const std::vector<int>& lslotf,
-                const std::vector<double>& lc) {
-    if (d->arena || d->storage == LBM_STORE_F16NODE || d->rule == LBM_RULE_ZHAO_YONG)
-        return LBM_OK;
+int plan_blocks(lbm_domain* d, const LinkTables& lt) {
+    if (d->arena || !domain_blockable(d)) return LBM_OK;
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return LBM_EDEVICE;
     int steps = 0;
-    double best = single_us(d);
+    double best = single_us(d->esize, (double)d->fluid);
     for (int k = 2; k <= kBlockSteps; ++k) {
-        const int halo = k * block_reach(d);
-        const int ow = kBlockW - 2 * halo, oh = kBlockH - 2 * halo;
-        if (ow < 4 || oh < 4) break;
-        const long long n = (long long)((d->nx + ow - 1) / ow) * ((d->ny + oh - 1) / oh);
+        const long long n = domain_block_tiles(d, k);
+        if (n == 0) break;
         const double us = block_us(d, k, n, ncu);
         if (us < best) {
             best = us;
@@ -784,7 +806,7 @@ int plan_blocks(lbm_domain* d, const std::vector<int>& lnode, const std::vector<
         }
     }
     BlockTables b;
-    if (steps == 0 || !block_tables(d, steps, lnode, lmeta, lslotb, lslotf, lc, b)) return LBM_OK;
+    if (steps == 0 || !block_tables(d, steps, lt, b)) return LBM_OK;
     BlockPlan& p = d->block;
     int rc;
     if ((rc = upload(d, &p.tiles, b.tiles)) || (rc = upload(d, &p.links, b.links)) ||
@@ -794,17 +816,8 @@ int plan_blocks(lbm_domain* d, const std::vector<int>& lnode, const std::vector<
     for (MassPart*& q : p.partial)
         if ((rc = dev_alloc(d, (void**)&q, (size_t)steps * nt * sizeof(MassPart)))) return rc;
     if (hipStreamSynchronize(d->stream) != hipSuccess) return LBM_EDEVICE;  // the tables end here
-    p.halo = b.halo;
-    p.pull = b.pull;
-    p.nstrips = b.nstrips;
-    p.nsegs = b.nsegs;
-    p.ntiles = nt;
+    block_plan(d, b);
     p.wide = nt <= ncu;
-    p.max_nodes = b.max_nodes;
-    p.max_len = b.max_len;
-    p.link_bytes = (unsigned)(b.links.size() * sizeof(BlockLink));
-    p.node_bytes = (unsigned)(b.nodes.size() * sizeof(BlockNode));
-    p.steps = steps;
     return LBM_OK;
 }
 
@@ -1202,7 +1215,10 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if ((rc = upload(d, &d->lc, lc))) return rc;
     if ((rc = upload(d, &d->luw, luw))) return rc;
     if (!lref.empty() && (rc = upload(d, &d->lref, lref))) return rc;
-    if ((rc = plan_blocks(d, lnode, lmeta, lslotb, lslotf, lc))) return rc;
+    LinkTables lt{std::move(lnode), std::move(lmeta), std::move(lslotb), std::move(lslotf),
+                  std::move(lc)};
+    if ((rc = plan_blocks(d, lt))) return rc;
+    if (d->arena && domain_blockable(d)) d->links = lt;  // (see domain_make_blocks)
     if ((rc = dev_alloc(d, (void**)&d->force,
                         (size_t)2 * std::max(link_blocks(d), 1) * 8)))
         return rc;
@@ -1303,6 +1319,44 @@ int domain_set_tiles(lbm_domain* d, int tile_w, int tile_h) {
     d->nsegs = ng;
     d->nblocks = ns * ng;
     return LBM_OK;
+}
+
+bool domain_make_blocks(lbm_domain* d, int steps, Arena* pool) {
+    domain_drop_blocks(d, pool);
+    BlockTables b;
+    if (!domain_blockable(d) || !block_tables(d, steps, d->links, b)) return false;
+    BlockPlan& p = d->block;
+    const size_t nt = (size_t)b.nstrips * b.nsegs;
+    p.tiles = static_cast<BlockTile*>(pool->alloc(nt * sizeof(BlockTile)));
+    p.links = static_cast<BlockLink*>(pool->alloc(b.links.size() * sizeof(BlockLink)));
+    p.nodes = static_cast<BlockNode*>(pool->alloc(b.nodes.size() * sizeof(BlockNode)));
+    p.partial[0] = static_cast<MassPart*>(pool->alloc((size_t)steps * nt * sizeof(MassPart)));
+    bool ok = p.tiles && p.links && p.nodes && p.partial[0];
+    auto put = [&](void* dst, const void* src, size_t n) {
+        if (ok && n)
+            ok = hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, d->stream) == hipSuccess;
+    };
+    put(p.tiles, b.tiles.data(), nt * sizeof(BlockTile));
+    put(p.links, b.links.data(), b.links.size() * sizeof(BlockLink));
+    put(p.nodes, b.nodes.data(), b.nodes.size() * sizeof(BlockNode));
+    // (the tables end with this call)
+    if (hipStreamSynchronize(d->stream) != hipSuccess) ok = false;
+    if (!ok) {
+        domain_drop_blocks(d, pool);
+        return false;
+    }
+    p.set = 0;
+    block_plan(d, b);
+    return true;
+}
+
+void domain_drop_blocks(lbm_domain* d, Arena* pool) {
+    BlockPlan& p = d->block;
+    for (void* q : {(void*)p.tiles, (void*)p.links, (void*)p.nodes, (void*)p.partial[0]})
+        pool->release(q);
+    const bool moving = p.moving;
+    p = BlockPlan{};
+    p.moving = moving;
 }
 
 Ctx domain_ctx(lbm_domain* d) { return ctx(d); }

@@ -109,3 +109,54 @@ def test_mass_does_not_depend_on_the_tiles(L, storage):
             got.append(d.mass_history())
     say(f"[gpu] masses for four tile shapes, {storage}: {got[0][-1]!r}")
     assert all(np.array_equal(got[0], g) for g in got[1:])
+
+
+def _mixed(eos):
+    """Instances of a batch, some of which break down within the run: with the
+    mean density at the walls and a tau near a half the droplets do."""
+    if eos == "none":
+        return [cfg.couette(10, rule="mls", fix="A"), cfg.sloped_channel(16, fix="B", g0=1e-3),
+                cfg.sloped_channel(44, rule="ibb_quadratic", fix="A", g0=1e-3)]
+    ps = []
+    for k, tau in enumerate((0.505, 0.52, 0.55, 0.9, 0.505, 0.55)):
+        p = cfg.batch_instance(k, seed=11, side_lo=40, side_hi=90)
+        mean = 0.5 * (p.rho0.max() + p.rho0.min())
+        ps.append(p.with_(tau=tau, collision="bgk", rho_wall=np.full_like(p.rho_wall, mean)))
+    return ps
+
+
+@pytest.mark.parametrize("runs", [RUNS + (46,), (94,)], ids=["short", "long"])
+@pytest.mark.parametrize("storage,eos", [(s, "cs") for s in STORAGES] + [("f64", "none")])
+def test_batch(L, storage, eos, runs):
+    ps = _mixed(eos)
+    total = [90, 33, 94, 12, 61, 94][:len(ps)]
+    say(f"[gpu] batch in blocks vs single steps {storage} {eos} {[p.nx for p in ps]}")
+    with L.Batch(storage=storage, eos=eos, max_instances=8, arena_bytes=1 << 28) as b:
+        slots = [b.add(p, n, history_capacity=128) for p, n in zip(ps, total)]
+        doms = [L.Domain(p, storage=storage, history_capacity=128) for p in ps]
+        try:
+            for d in doms:
+                L.lbm_set_profiling(d.h, 1)  # single steps
+            for n in runs:
+                b.run(n)
+                for k, d in enumerate(doms):
+                    t, rem, u = b.status(slots[k])
+                    if L.lbm_unstable_step(d.h) < 0:
+                        try:
+                            d.step(min(n, total[k] - d.t))
+                        except L.LbmError as e:
+                            assert e.code == L.LBM_EUNSTABLE
+                    alone = L.lbm_unstable_step(d.h)
+                    assert u == alone, (k, u, alone)
+                    assert t == (u if u >= 0 else d.t) and rem == (0 if u >= 0 else total[k] - t)
+                    if u < 0:
+                        for x, y in zip(b.moments(slots[k]), d.moments()):
+                            assert np.array_equal(x, y, equal_nan=True), (k, t)
+                    h = b.mass_history(slots[k])
+                    assert np.array_equal(h, d.mass_history()[:len(h)], equal_nan=True), (k, t)
+            ends = [b.status(s)[2] for s in slots]
+            say(f"    unstable at {ends}")
+            assert eos == "none" or (max(ends) > 0 and min(ends) < 0)
+        finally:
+            for d in doms:
+                d.close()
