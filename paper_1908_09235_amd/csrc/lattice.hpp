@@ -141,18 +141,22 @@ __host__ __device__ __forceinline__ float root(float x) {
 
 // Pseudopotential.  EXP: psi0 exp(-rho0/rho).  CS: sqrt(2 (p - rho/3)/G)
 // with p the Carnahan-Starling pressure.  p2G = 2/G.
+template <typename R>
+__host__ __device__ __forceinline__ R cs_psi_squared(R rho, const Phys<R>& p) {
+    const R a = p.e0, b = p.e1, Rg = p.e2, T = p.e3;
+    const R eta = R(0.25) * b * rho;
+    const R num = fma(eta, fma(eta, R(1) - eta, R(1)), R(1));
+    const R om = R(1) - eta;
+    const R den = om * om * om;
+    const R pe = fma(-a * rho, rho, (rho * Rg * T) * num * rcp(den));
+    return p.p2G * fma(rho, R(-1.0 / 3.0), pe);
+}
 template <int EOS, typename R>
 __host__ __device__ __forceinline__ R psi_of(R rho, const Phys<R>& p) {
     if constexpr (EOS == EOS_EXP) {
         return p.e0 * exp(-p.e1 * rcp(rho));
     } else if constexpr (EOS == EOS_CS) {
-        const R a = p.e0, b = p.e1, Rg = p.e2, T = p.e3;
-        const R eta = R(0.25) * b * rho;
-        const R num = fma(eta, fma(eta, R(1) - eta, R(1)), R(1));
-        const R om = R(1) - eta;
-        const R den = om * om * om;
-        const R pe = fma(-a * rho, rho, (rho * Rg * T) * num * rcp(den));
-        return root(p.p2G * fma(rho, R(-1.0 / 3.0), pe));
+        return root(cs_psi_squared(rho, p));
     } else {
         return R(0);
     }

@@ -217,3 +217,57 @@ def test_state_buffer_limit_is_enforced_at_create(L, storage):
     assert L.lib().lbm_create_domain(ctypes.byref(d), ctypes.byref(h)) == L.LBM_EINVAL
     d.nx, d.ny = 1 << 15, 1 << 15
     assert L.lib().lbm_create_domain(ctypes.byref(d), ctypes.byref(h)) == L.LBM_EINVAL
+
+
+@pytest.mark.parametrize("nx,ny", [(3, 3), (3, 40), (17, 5), (64, 65)])
+def test_links_are_counted_over_the_seams(L, nx, ny):
+    """The links have to be all those of the lattice, also across its periodic
+    seams and where solid nodes carry other values than one.  (What passes the
+    checks ends with another code here, or not at all with a GPU.)"""
+    rng = np.random.default_rng(nx * ny)
+    solid = (rng.random((ny, nx)) < 0.3).astype(np.uint8)
+    solid[0, 0], solid[-1, -1], solid[ny // 2, nx // 2] = 1, 1, 0
+    cx, cy = (0, 1, 0, -1, 0, 1, -1, -1, 1), (0, 0, 1, 0, -1, 1, 1, -1, -1)
+    links = [(x, y, a) for y in range(ny) for x in range(nx) for a in range(1, 9)
+             if not solid[y, x] and solid[(y + cy[a]) % ny, (x + cx[a]) % nx]]
+    d = L.lbm_desc()
+    d.nx, d.ny, d.tau, d.storage = nx, ny, 0.8, L.STORAGE["f64"]
+    d.rho_wall_const = 1.0
+    raw = (solid * rng.integers(1, 256, solid.shape)).astype(np.uint8)
+    rho = np.ones((ny, nx))
+    table = (L.lbm_link * len(links))()
+    for t, (x, y, a) in zip(table, links):
+        t.x, t.y, t.dir, t.q = x, y, a, 0.5
+    d.solid = raw.ctypes.data_as(type(d.solid))
+    d.rho0 = rho.ctypes.data_as(type(d.rho0))
+    d.links = ctypes.cast(table, type(d.links))
+
+    def code(n):
+        h = ctypes.c_void_p()
+        d.nlinks = n
+        rc = L.lib().lbm_create_domain(ctypes.byref(d), ctypes.byref(h))
+        if rc == L.LBM_OK:
+            L.lib().lbm_destroy(h)
+        return rc
+
+    assert code(len(links)) != L.LBM_EINVAL
+    assert code(len(links) - 1) == L.LBM_EINVAL
+
+
+@pytest.mark.parametrize("nx", [3, 7, 64])
+def test_densities_without_a_potential_are_refused(L, nx):
+    """Carnahan-Starling with G = -1: the square of psi is negative where the
+    pressure exceeds rho/3, infinite at b rho = 4; at solid nodes neither
+    counts."""
+    p = cfg.free_droplet(nx, 0.25 * nx)
+    b = p.eos_params[1]
+    for bad, at in ((3.6 / b, (1, 1)), (4.0 / b, (0, nx - 1)), (np.inf, (2, 0))):
+        rho = p.rho0.copy()
+        rho[at] = bad
+        with pytest.raises(L.LbmError) as e:
+            L.Domain(p.with_(rho0=rho), storage="f64")
+        assert e.value.code == L.LBM_EINVAL
+    try:
+        L.Domain(p, storage="f64").close()
+    except L.LbmError as e:
+        assert e.code != L.LBM_EINVAL
