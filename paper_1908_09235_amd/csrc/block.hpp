@@ -55,8 +55,9 @@ constexpr unsigned block_lds(int n) { return 32u * (unsigned)n; }
 // Per tile: records of the cut links whose fluid node lies in the region
 // (groups of one node together, none across a chunk of 64) and of the nodes
 // whose moments the wall rules read.
-struct BlockTile {
+struct alignas(32) BlockTile {
     int link0, chunks, node0, nodes;
+    int x0, y0, cols, rows;  // its own nodes
 };
 struct alignas(16) BlockLink {
     int meta;             // as BndArgs::lmeta; LK_PAD: padding
@@ -76,7 +77,7 @@ struct alignas(8) BlockNode {
 // Strip and segment of a tile: bands of 8 segments, strip by strip, so that
 // the tiles an XCD runs at a time (64, two per CU) form a patch of about 8 x
 // 8 and find most of their halos in its L2.
-__host__ __device__ __forceinline__ int2 block_place(int tile, int nstrips, int nsegs) {
+inline int2 block_place(int tile, int nstrips, int nsegs) {
     const int band = tile / (8 * nstrips), r = tile - band * 8 * nstrips;
     const int h = nsegs - 8 * band < 8 ? nsegs - 8 * band : 8;
     const int strip = r / h;
@@ -102,7 +103,7 @@ struct BlockArgs {
     int nx, ny, pitch;
     long long plane;
     int halo, pull;                        // pull: margin of a step's pull
-    int nstrips, ntiles, nsegs;
+    int ntiles;
     int max_nodes;                         // moment records of LDS
     unsigned mom_bytes, link_bytes, node_bytes;
     int open_x;
@@ -155,14 +156,8 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
     double* const leak = dyn + 3 * a.max_nodes;     // scheme A: [record]
 
     const int t = threadIdx.x;
-    const int2 place = block_place(tile, a.nstrips, a.nsegs);
-    const int strip = place.x, seg = place.y;
-    auto share = [](int k, int n, int parts) {
-        return (int)((unsigned long long)k * (unsigned)n / (unsigned)parts);
-    };
-    const int x0 = share(strip, a.nx, a.nstrips), y0 = share(seg, a.ny, a.nsegs);
-    const int ncols = share(strip + 1, a.nx, a.nstrips) - x0;
-    const int nrows = share(seg + 1, a.ny, a.nsegs) - y0;
+    const BlockTile bt = ro(a.tiles)[tile];
+    const int x0 = bt.x0, y0 = bt.y0, ncols = bt.cols, nrows = bt.rows;
     const int halo = a.halo, pull = a.pull;
     const int fix = a.fix, moving = a.moving, max_len = a.max_len;
     const int open_x = a.open_x, chi = a.chi;
@@ -189,11 +184,14 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         return (unsigned)wrap(y0 - halo + ly_at(t, j), ny, RH) * pitch + (unsigned)x_at(t, j, nx);
     };
 
-    // ---- all loads of the tile: the region of f*(t) (solid nodes' slots come
-    // along unread) while the tile's entry arrives, then its lists, then the
-    // moments they name.  No branch: a lane without a record reads past its
-    // buffer, which yields 0, so each wait leaves the later loads in flight.
-    const BlockTile bt = ro(a.tiles)[tile];
+    // ---- all loads of the tile: its lists first, then the region of f*(t)
+    // (solid nodes' slots come along unread), then the moments that the list
+    // names, which so travel with the region.  No branch: a lane without a
+    // record reads past its buffer, which yields 0, so each wait leaves the
+    // later loads in flight.  (The lists after the region, and the tile's place from
+    // four 64-bit divisions instead of its entry: 1700 cycles more a launch;
+    // 2048^2 FP64 2110 -> 1997 us per 20 steps, 6 sessile droplets 4780 ->
+    // 4490 per 192.)
     const rsrc_t rli = make_rsrc(a.links, a.link_bytes), rno = make_rsrc(a.nodes, a.node_bytes);
     const rsrc_t rmo = make_rsrc(cur ? a.mom[1] : a.mom[0], a.mom_bytes);
     uint4_t l0, l1;
@@ -203,6 +201,13 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
     unsigned info = 0;
     auto fact = [&](int j) { return info >> (16 * j); };
     {
+        const bool has_link = (t >> 6) < bt.chunks, has_node = t < bt.nodes;
+        const uint2_t nd =
+            bload<uint2_t>(rno, has_node ? (unsigned)(bt.node0 + t) * 8u : kOOB, 0u);
+        const unsigned lo =
+            has_link ? (unsigned)(bt.link0 + t) * (unsigned)sizeof(BlockLink) : kOOB;
+        l0 = bload<uint4_t>(rli, lo, 0u);
+        l1 = bload<uint4_t>(rli, lo, 16u);
         S g[NPT][9];
         uint8_t fl[NPT];
         float pw[NPT];
@@ -214,13 +219,6 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
 #pragma unroll
             for (int q = 0; q < 9; ++q) g[j][q] = bload<S>(rs, o * ES, q * pb);
         }
-        const bool has_link = (t >> 6) < bt.chunks, has_node = t < bt.nodes;
-        const uint2_t nd =
-            bload<uint2_t>(rno, has_node ? (unsigned)(bt.node0 + t) * 8u : kOOB, 0u);
-        const unsigned lo =
-            has_link ? (unsigned)(bt.link0 + t) * (unsigned)sizeof(BlockLink) : kOOB;
-        l0 = bload<uint4_t>(rli, lo, 0u);
-        l1 = bload<uint4_t>(rli, lo, 16u);
         // the moment record of each node, until psi takes the place
         unsigned short* const rec = reinterpret_cast<unsigned short*>(psb);
 #pragma unroll

@@ -89,8 +89,6 @@ BlockArgs block_args(const lbm_domain* d) {
     a.plane = d->plane;
     a.halo = p.halo;
     a.pull = p.pull;
-    a.nstrips = p.nstrips;
-    a.nsegs = p.nsegs;
     a.ntiles = p.ntiles;
     a.max_nodes = p.max_nodes;
     a.mom_bytes = (unsigned)(3 * std::max(d->nslots, 1) * 8);
@@ -798,7 +796,7 @@ bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTab
         if (chunks > kBlockThreads / 64 || nn > kBlockNodes || b.links.size() >= (1u << 25))
             return false;
         b.max_nodes = std::max(b.max_nodes, nn);
-        b.tiles[(size_t)i] = BlockTile{link0, chunks, node0, nn};
+        b.tiles[(size_t)i] = BlockTile{link0, chunks, node0, nn, x0, y0, x1 - x0, y1 - y0};
     }
     return true;
 }
