@@ -276,8 +276,7 @@ int plan_batch(lbm_batch* b) {
     if (!any) return 0;
     double best = 28.0 + 18.0 * (double)any->esize * fluid * 1e-6 / 5.2;
     int steps = 0;
-    const bool arith64 = b->bd.storage == LBM_STORE_F64 || b->bd.storage == LBM_STORE_F32;
-    const double part = !arith64 ? 0.75 : any->esize == 8 ? 0.92 : 0.78;
+    const double part = any->esize == 2 ? 1.05 : 0.9;
     auto cost = [&](int k) {  // (and the reduction's launch)
         const long long more = std::max<long long>(tiles[k] - b->ncu, 0);
         return block_us(any, k, std::min<long long>(tiles[k], b->ncu) + (long long)(part * more),

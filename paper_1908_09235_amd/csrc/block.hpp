@@ -21,17 +21,16 @@
 //   collide  force, moments and collision, written back in place (the rest
 //            population never leaves its thread), on the last step to HBM.
 //
-// What bounds it.  Small lattices: latency.  A launch takes about 6.6 us (its
-// start, two rounds of loads, the stores) and a step about 3.3 us on a CU of
-// its own, against 11 to 17 us a step for a boundary and a main launch:
-// droplet 128^2 in FP64, us a step, single steps 16.3, 2 per launch 6.6, 4 per
-// launch 4.9, 6 per launch 4.4 (4.0 with 1024 lanes).  Large lattices: the
-// wavefronts in flight (FP64 populations of two regions fill a CU's LDS) and
-// the arithmetic of the halos, 1.3 times a single step's with 2 steps per
-// launch; HBM traffic is halved (331 MB read and 275 MB written per 2 steps
-// at 2048^2 in FP64, counted).  At 2048^2: FP64 storage 132 -> 96, FP32 with
-// FP64 arithmetic 75 -> 80 (not used there), FP32 arithmetic 75 -> 65;
-// single phase, 4 steps, FP64 140 -> 63.
+// What bounds it.  Small lattices: latency.  A launch takes about 6 us (its
+// start, the loads, the stores) and a step about 2 us on a CU of its own,
+// against 9 to 13 us a step for a boundary and a main launch: droplet 128^2 in
+// FP64, us a step, single steps 11.0, 2 per launch 5.6, 4 per launch 4.1, 6 per
+// launch 3.5.  Large lattices: the wavefronts in flight (FP64 populations of
+// two regions fill a CU's LDS) and the arithmetic of the halos, 1.3 times a
+// single step's with 2 steps per launch; HBM traffic is halved (331 MB read
+// and 275 MB written per 2 steps at 2048^2 in FP64, counted).  At 2048^2: FP64
+// storage 141 -> 92, FP32 with FP64 arithmetic 77 -> 79 (not used there), FP32
+// arithmetic 75 -> 55; single phase, 4 steps, FP64 140 -> 60.
 //
 // Why 32 x 32: the largest square region of which two fit a CU's 160 KB in
 // FP64 (8 x 8 bytes of moving populations and 8 of psi a node; the rest
@@ -47,7 +46,10 @@ namespace lbm {
 
 constexpr int kBlockSteps = 8;  // at most, per launch
 constexpr int kBlockBins = 16;   // LDS bins of a step's mass
-constexpr int kBlockW = 32, kBlockH = 32, kBlockThreads = 512;
+constexpr int kBlockThreads = 512;
+// the side of the square region that a workgroup of `lanes` threads works on
+constexpr int kBlockSmall = 576;  // (24 x 24, one node a lane)
+constexpr int block_side(int lanes) { return lanes == kBlockSmall ? 24 : 32; }
 constexpr int kBlockNodes = kBlockThreads;  // moment records of a tile: one a thread
 // bytes of LDS for n moment records and their leaks
 constexpr unsigned block_lds(int n) { return 32u * (unsigned)n; }
@@ -134,15 +136,15 @@ __device__ __forceinline__ Phys<R> block_phys(const LBM_CONST_AS BlockArgs& a) {
 // fill its LDS), three with FP32 arithmetic, which fits 80 registers.
 template <typename R>
 constexpr int block_waves(int nt) {
-    return sizeof(R) == 4 && nt == kBlockThreads ? 6 : 4;
+    return nt == kBlockSmall ? 3 : sizeof(R) == 4 && nt == kBlockThreads ? 6 : 4;
 }
 
 // `steps` steps of tile `tile` of the domain described at ka (uniform, in
 // memory that no launch writes), whose f*(t) lies in f[cur].
-template <typename S, typename R, int EOS, int DEV, int RW, int RH, int NT>
+template <typename S, typename R, int EOS, int DEV, int NT>
 __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int steps, int tile) {
     static_assert(DEV == 0 || DEV == 1, "per-node references are not blocked");
-    constexpr int NN = RW * RH, NPT = NN / NT, NW = NT / 64;
+    constexpr int RW = block_side(NT), RH = RW, NN = RW * RH, NPT = NN / NT, NW = NT / 64;
     static_assert(NN % NT == 0 && NT % 64 == 0, "every thread has as many nodes");
     constexpr unsigned ES = sizeof(S);
     constexpr int NP = EOS == EOS_NONE ? (NN * 2 + (int)sizeof(R) - 1) / (int)sizeof(R) : NN;
@@ -531,8 +533,8 @@ k_block(BlockKernarg k) {
 #else
     const BlockArgs* args = &k.a;
 #endif
-    block_tile<S, R, EOS, DEV, kBlockW, kBlockH, NT>(args, k.r.cur, k.r.steps,
-                                                     xcd_tile(blockIdx.x, k.a.ntiles));
+    block_tile<S, R, EOS, DEV, NT>(args, k.r.cur, k.r.steps,
+                                   xcd_tile(blockIdx.x, k.a.ntiles));
 }
 
 // ---------------------------------------------------------------- batches
@@ -562,7 +564,7 @@ __global__ __launch_bounds__(kBlockThreads)
     const BState st = ro<BState>(b.state)[te.x];
     const int n = block_steps(st.remaining, st.hold, b.steps);
     if (n <= 0) return;
-    block_tile<S, R, EOS, DEV, kBlockW, kBlockH, kBlockThreads>(b.inst + te.x, st.cur, n, te.y);
+    block_tile<S, R, EOS, DEV, kBlockThreads>(b.inst + te.x, st.cur, n, te.y);
 }
 
 // Per instance: the masses of the launch and the state it leaves.

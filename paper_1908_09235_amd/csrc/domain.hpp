@@ -45,7 +45,7 @@ struct BlockPlan {
     int nstrips = 0, nsegs = 0, ntiles = 0, max_nodes = 0, max_len = 0;
     unsigned link_bytes = 0, node_bytes = 0;
     bool moving = false;
-    bool wide = false;   // 1024 lanes per tile
+    int lanes = kBlockThreads;  // per tile (see block_t)
     BlockTile* tiles = nullptr;
     BlockLink* links = nullptr;
     BlockNode* nodes = nullptr;
@@ -161,7 +161,7 @@ Ctx domain_ctx(lbm_domain* d);
 // single steps.
 bool domain_blockable(const lbm_domain* d);
 // Tiles of a launch of `steps` steps (0: its halos leave none).
-long long domain_block_tiles(const lbm_domain* d, int steps);
+long long domain_block_tiles(const lbm_domain* d, int steps, int lanes = kBlockThreads);
 // The tables of `steps` steps per launch for an instance of a batch, in memory
 // of `pool` (false if it has none left or the tables do not fit a tile; the
 // instance has no plan then).  Waits for the instance's stream.
@@ -176,15 +176,20 @@ BlockArgs block_args(const lbm_domain* d);
 //   single: two launches and the populations at 4.6 TB/s (FP16 at 3.7);
 //     measured in FP64 / FP32 / FP16 storage: 13.3 / 12.2 / 12 at 400^2,
 //     31.4 / 24.7 / 20 at 1024^2, 132 / 75 / 48 at 2048^2.
-//   k_block: 6.6 us a launch and 3.3 a step while every tile has a CU of its
-//     own, then a cost per further tile, of which the two-phase step, FP64
-//     arithmetic and the halos (a step more shrinks the tiles) are the parts.
-//     Measured for the droplet in FP64 storage: 6 steps at 128^2 4.4 a step,
-//     3 at 400^2 7.6, 2 at 1024^2 26.3, 2 at 2048^2 96; in FP32 storage with
-//     FP64 arithmetic 18.2 at 800^2, 24.9 at 1024^2, 80 at 2048^2 (arithmetic
-//     of the halos: single steps are faster from 1024^2 on).
+//   k_block: so much a launch and a step while every tile has a CU of its own,
+//     then a cost per further tile, of which FP64 arithmetic, the two-phase
+//     step and the halos (a step more shrinks the tiles) are the parts.
+//     Measured, us a step with the number of steps taken (single steps):
+//     droplets, FP64: 3.5 with 6 at 128^2 (11.0), 6.8 with 3 at 400^2 (13.1),
+//     24.2 with 2 at 1024^2 (32.4), 91.9 with 2 at 2048^2 (140.7); FP32 with
+//     FP64 arithmetic: 22.2 with 2 at 1024^2 (24.6), 79.3 with 2 at 2048^2
+//     (77.1: the arithmetic of the halos); FP32: 14.3 and 54.8 (21.5, 75.3);
+//     FP16 deviations: 15.0 and 43.6 (20.5, 44.3).  Single phase at 2048^2:
+//     FP64 60.0 with 4 (139.6), FP32 with FP64 arithmetic 52.8 with 3 (75.2),
+//     FP32 35.0 with 4 (75.1), FP16 deviations 36.6 with 3 (41.0).
 double single_us(size_t esize, double fluid);
-double block_us(const lbm_domain* d, int steps, long long tiles, int ncu);
+double block_us(const lbm_domain* d, int steps, long long tiles, int ncu,
+                int lanes = kBlockThreads);
 // The buffer the moments at the current time are pulled from: f*(t - 1)
 // with the ghosts of step t (after a two-step pass, rebuilt by a replay of
 // step t - 1 into the domain's replay buffer; also forms the wall force of

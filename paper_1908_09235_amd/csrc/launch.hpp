@@ -52,10 +52,10 @@ void launch_main_f32(const Ctx& c, const void* src, void* dst, bool moments);
 // two steps per pass src -> dst (storage forms with FP32 or FP16
 // populations and one reference density; see fused.hpp)
 void launch_main2_f32(const Ctx& c, const void* src, void* dst);
-// several steps per launch (see block.hpp): 1024 lanes per tile (wide) or
-// 512; lds: bytes of dynamic LDS
-void launch_block_f64(const Ctx& c, const BlockKernarg& k, bool wide, unsigned lds);
-void launch_block_f32(const Ctx& c, const BlockKernarg& k, bool wide, unsigned lds);
+// several steps per launch (see block.hpp) with 512, 1024 or 576 lanes per
+// tile; lds: bytes of dynamic LDS
+void launch_block_f64(const Ctx& c, const BlockKernarg& k, int lanes, unsigned lds);
+void launch_block_f32(const Ctx& c, const BlockKernarg& k, int lanes, unsigned lds);
 // one boundary pass on cur
 void launch_boundary_f64(const Ctx& c, void* cur, const BndArgs& b, int nblocks);
 void launch_boundary_f32(const Ctx& c, void* cur, const BndArgs& b, int nblocks);

@@ -3,12 +3,12 @@
 
 namespace lbm {
 
-void launch_block_f32(const Ctx& c, const BlockKernarg& k, bool wide, unsigned lds) {
+void launch_block_f32(const Ctx& c, const BlockKernarg& k, int lanes, unsigned lds) {
     switch (c.storage) {
-    case 2: block_any<float, float, 0>(c, k, wide, lds); break;
-    case 3: block_any<float, float, 1>(c, k, wide, lds); break;
-    case 4: block_any<_Float16, float, 1>(c, k, wide, lds); break;
-    default: block_any<float, double, 0>(c, k, wide, lds);
+    case 2: block_any<float, float, 0>(c, k, lanes, lds); break;
+    case 3: block_any<float, float, 1>(c, k, lanes, lds); break;
+    case 4: block_any<_Float16, float, 1>(c, k, lanes, lds); break;
+    default: block_any<float, double, 0>(c, k, lanes, lds);
     }
 }
 

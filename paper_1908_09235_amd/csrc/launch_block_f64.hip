@@ -3,8 +3,8 @@
 
 namespace lbm {
 
-void launch_block_f64(const Ctx& c, const BlockKernarg& k, bool wide, unsigned lds) {
-    block_any<double, double, 0>(c, k, wide, lds);
+void launch_block_f64(const Ctx& c, const BlockKernarg& k, int lanes, unsigned lds) {
+    block_any<double, double, 0>(c, k, lanes, lds);
 }
 
 void launch_block_batch_f64(const BlockBatchLaunch& L) { block_batch_any<double, double, 0>(L); }

@@ -38,27 +38,36 @@ bool domain_blockable(const lbm_domain* d) {
     return d->storage != LBM_STORE_F16NODE && d->rule != LBM_RULE_ZHAO_YONG;
 }
 
-long long domain_block_tiles(const lbm_domain* d, int steps) {
-    const int halo = steps * block_reach(d);
-    const int ow = kBlockW - 2 * halo, oh = kBlockH - 2 * halo;
-    if (ow < 4 || oh < 4) return 0;
-    return (long long)((d->nx + ow - 1) / ow) * ((d->ny + oh - 1) / oh);
+long long domain_block_tiles(const lbm_domain* d, int steps, int lanes) {
+    const int own = block_side(lanes) - 2 * steps * block_reach(d);
+    if (own < 4) return 0;
+    return (long long)((d->nx + own - 1) / own) * ((d->ny + own - 1) / own);
 }
 
 double single_us(size_t esize, double fluid) {
     return 8.0 + 18.0 * (double)esize * fluid * 1e-6 / (esize == 2 ? 3.7 : 4.6);
 }
 
-double block_us(const lbm_domain* d, int steps, long long tiles, int ncu) {
+double block_us(const lbm_domain* d, int steps, long long tiles, int ncu, int lanes) {
     const bool two_phase = d->eos != EOS_NONE;
-    const bool arith64 = d->storage == LBM_STORE_F64 || d->storage == LBM_STORE_F32;
-    double us = 6.6 + 3.3 * steps;
-    if (tiles > ncu) {
-        const double per = two_phase ? (arith64 ? 0.0175 + 0.0037 * steps : 0.0105 + 0.0031 * steps)
-                                     : (d->esize == 8 ? 0.0245 + 0.0023 * steps
-                                                      : 0.0145 + 0.0040 * steps);
-        us += 5.0 + per * (double)(tiles - ncu);
-    }
+    struct Cost {
+        double launch, step, shared;  // with a CU for each tile; more where tiles share one
+        double tile, tile_step;       // each tile more than CUs
+    };
+    static const Cost costs[2][4] = {{{5.9, 2.1, 7.0, 0.0175, 0.0033},    // single phase: FP64
+                                      {5.9, 2.1, 7.0, 0.0115, 0.0043},    // FP32, arithmetic FP64
+                                      {5.4, 1.8, 7.0, 0.0135, 0.0014},    // FP32
+                                      {5.4, 1.8, 7.0, 0.0046, 0.0033}},   // FP16
+                                     {{6.4, 2.45, 4.0, 0.0163, 0.0037},   // two phases
+                                      {6.4, 2.45, 4.0, 0.0095, 0.0053},
+                                      {5.0, 2.05, 2.0, 0.0115, 0.0018},
+                                      {5.0, 2.05, 2.0, 0.0046, 0.0033}}};
+    const Cost& c = costs[two_phase][d->esize == 8                   ? 0
+                                     : d->storage == LBM_STORE_F32   ? 1
+                                     : d->esize == 4                 ? 2
+                                                                     : 3];
+    double us = (c.launch + c.step * steps) * (lanes == kBlockSmall ? 0.85 : 1.0);
+    if (tiles > ncu) us += c.shared + (c.tile + c.tile_step * steps) * (double)(tiles - ncu);
     return us / steps;
 }
 
@@ -461,8 +470,8 @@ void launch_block(lbm_domain* d, int k) {
     p.set ^= 1;
     arg.a = block_args(d);
     const unsigned lds = block_lds(p.max_nodes);
-    if (d->storage == LBM_STORE_F64) launch_block_f64(ctx(d), arg, p.wide, lds);
-    else launch_block_f32(ctx(d), arg, p.wide, lds);
+    if (d->storage == LBM_STORE_F64) launch_block_f64(ctx(d), arg, p.lanes, lds);
+    else launch_block_f32(ctx(d), arg, p.lanes, lds);
     d->cur ^= 1;
     d->t += k;
     d->pending = true;
@@ -562,7 +571,7 @@ int run_steps(lbm_domain* d, int64_t n) {
             const int k = (int)std::min<int64_t>(n - 1, d->block.steps);
             // (a launch of one step costs more than a pass, but for the
             // smallest domains, where the launches are the cost)
-            if (k == 1 && !d->block.wide) launch_pass(d, false, nullptr);
+            if (k == 1 && d->block.lanes == kBlockThreads) launch_pass(d, false, nullptr);
             else launch_block(d, k);
             n -= k;
         }
@@ -667,7 +676,7 @@ struct LinkRec {
 // nodes whose moments they read.  False if a tile holds more than a workgroup
 // has lanes or LDS for.
 struct BlockTables {
-    int steps = 0, halo = 0, pull = 0, nstrips = 0, nsegs = 0, max_nodes = 0, max_len = 0;
+    int steps = 0, lanes = 0, halo = 0, pull = 0, nstrips = 0, nsegs = 0, max_nodes = 0, max_len = 0;
     std::vector<BlockTile> tiles;
     std::vector<BlockLink> links;
     std::vector<BlockNode> nodes;
@@ -685,19 +694,22 @@ void block_plan(lbm_domain* d, const BlockTables& b) {
     p.link_bytes = (unsigned)(b.links.size() * sizeof(BlockLink));
     p.node_bytes = (unsigned)(b.nodes.size() * sizeof(BlockNode));
     p.steps = b.steps;
+    p.lanes = b.lanes;
 }
-bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTables& b) {
+bool block_tables(const lbm_domain* d, int steps, int lanes, const LinkTables& lt, BlockTables& b) {
     const std::vector<int>&lnode = lt.node, &lmeta = lt.meta, &lslotb = lt.slotb,
                     &lslotf = lt.slotf;
     const std::vector<double>& lc = lt.c;
     b = BlockTables{};
     b.steps = steps;
+    b.lanes = lanes;
+    const int W = block_side(lanes);
     b.pull = block_pull(d);
     b.halo = steps * block_reach(d);
-    const int ow = kBlockW - 2 * b.halo, oh = kBlockH - 2 * b.halo;
-    if (ow < 1 || oh < 1) return false;
-    b.nstrips = (d->nx + ow - 1) / ow;
-    b.nsegs = (d->ny + oh - 1) / oh;
+    const int own = W - 2 * b.halo;
+    if (own < 1) return false;
+    b.nstrips = (d->nx + own - 1) / own;
+    b.nsegs = (d->ny + own - 1) / own;
     if ((long long)b.nstrips * b.nsegs >= (1 << 24)) return false;
     // the regions (and the place in them) that pull a column or row
     auto places = [&](int n, int parts, int width) {
@@ -709,7 +721,7 @@ bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTab
         }
         return v;
     };
-    const auto X = places(d->nx, b.nstrips, kBlockW), Y = places(d->ny, b.nsegs, kBlockH);
+    const auto X = places(d->nx, b.nstrips, W), Y = places(d->ny, b.nsegs, W);
     auto tile_of = [&](int strip, int seg) {
         const int band = seg / 8, h = std::min(8, b.nsegs - 8 * band);
         return band * 8 * b.nstrips + strip * h + (seg - 8 * band);
@@ -727,7 +739,7 @@ bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTab
             }
             for (const auto& y : Y[(size_t)(lnode[k] / P)])
                 for (const auto& x : X[(size_t)(lnode[k] % P)])
-                    take(tile_of(x.first, y.first), (int)k, y.second * kBlockW + x.second);
+                    take(tile_of(x.first, y.first), (int)k, y.second * W + x.second);
             k += (size_t)((lmeta[k] >> 8) & 15);
         }
     };
@@ -738,7 +750,7 @@ bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTab
         std::vector<int> at(first.begin(), first.end() - 1);
         images([&](int tile, int k, int l) { im[(size_t)at[(size_t)tile]++] = Image{k, l}; });
     }
-    std::vector<int> rec(kBlockW * kBlockH, -1);
+    std::vector<int> rec((size_t)W * W, -1);
     b.tiles.resize((size_t)nt);
     for (int i = 0; i < nt; ++i) {
         const int2 g = block_place(i, b.nstrips, b.nsegs);
@@ -746,21 +758,21 @@ bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTab
         const int y0 = (int)((long long)g.y * d->ny / b.nsegs);
         const int x1 = (int)((long long)(g.x + 1) * d->nx / b.nstrips);
         const int y1 = (int)((long long)(g.y + 1) * d->ny / b.nsegs);
-        auto own = [&](int l) {
-            const int lx = l % kBlockW - b.halo, ly = l / kBlockW - b.halo;
+        auto is_own = [&](int l) {
+            const int lx = l % W - b.halo, ly = l / W - b.halo;
             return lx >= 0 && lx < x1 - x0 && ly >= 0 && ly < y1 - y0;
         };
         const int link0 = (int)b.links.size(), node0 = (int)b.nodes.size();
         auto record = [&](int l, int slot) {
             if (rec[(size_t)l] < 0) {
                 rec[(size_t)l] = (int)b.nodes.size() - node0;
-                b.nodes.push_back(BlockNode{slot, (unsigned short)l, (unsigned char)own(l), 0});
+                b.nodes.push_back(BlockNode{slot, (unsigned short)l, (unsigned char)is_own(l), 0});
             }
             return rec[(size_t)l];
         };
         BlockLink pad{};
         pad.meta = LK_PAD << 4 | 1;
-        pad.xb = 2 * kBlockW + 2;
+        pad.xb = 2 * W + 2;
         for (int e = first[(size_t)i]; e < first[(size_t)i + 1]; ++e) {
             const int k0 = im[(size_t)e].k0, l = im[(size_t)e].at;
             const int len = (lmeta[(size_t)k0] >> 8) & 15;
@@ -773,14 +785,14 @@ bool block_tables(const lbm_domain* d, int steps, const LinkTables& lt, BlockTab
                 const int a = lmeta[(size_t)k] & 15;
                 int sf = 0;
                 if (lslotf[(size_t)k] >= 0)
-                    sf = record(l - cx(a) - cy(a) * kBlockW, lslotf[(size_t)k]);
+                    sf = record(l - cx(a) - cy(a) * W, lslotf[(size_t)k]);
                 BlockLink r{};
                 r.meta = lmeta[(size_t)k];
                 r.id = k;
                 r.xb = (unsigned short)l;
                 r.sb = (unsigned short)sb;
                 r.sf = (unsigned short)sf;
-                r.own = (unsigned short)own(l);
+                r.own = (unsigned short)is_own(l);
                 const double* const c = lc.data() + 8 * (size_t)k;
                 const bool chi = ((lmeta[(size_t)k] >> 4) & 15) <= LK_CHI_EXT;
                 r.k[0] = chi ? c[3] : c[0];
@@ -809,19 +821,23 @@ int plan_blocks(lbm_domain* d, const LinkTables& lt) {
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return LBM_EDEVICE;
-    int steps = 0;
+    int steps = 0, lanes = kBlockThreads;
     double best = single_us(d->esize, (double)d->fluid);
-    for (int k = 2; k <= kBlockSteps; ++k) {
-        const long long n = domain_block_tiles(d, k);
-        if (n == 0) break;
-        const double us = block_us(d, k, n, ncu);
-        if (us < best) {
-            best = us;
-            steps = k;
+    for (int n : {2 * kBlockThreads, kBlockSmall})
+        for (int k = 2; k <= kBlockSteps; ++k) {
+            const long long tiles = domain_block_tiles(d, k, n);
+            if (tiles == 0) continue;
+            if (n == kBlockSmall && (tiles > ncu || d->eos != EOS_NONE)) continue;
+            const int w = tiles <= ncu ? n : kBlockThreads;
+            const double us = block_us(d, k, tiles, ncu, w);
+            if (us < best) {
+                best = us;
+                steps = k;
+                lanes = w;
+            }
         }
-    }
     BlockTables b;
-    if (steps == 0 || !block_tables(d, steps, lt, b)) return LBM_OK;
+    if (steps == 0 || !block_tables(d, steps, lanes, lt, b)) return LBM_OK;
     BlockPlan& p = d->block;
     int rc;
     if ((rc = upload(d, &p.tiles, b.tiles)) || (rc = upload(d, &p.links, b.links)) ||
@@ -832,7 +848,6 @@ int plan_blocks(lbm_domain* d, const LinkTables& lt) {
         if ((rc = dev_alloc(d, (void**)&q, (size_t)steps * nt * sizeof(MassPart)))) return rc;
     if (hipStreamSynchronize(d->stream) != hipSuccess) return LBM_EDEVICE;  // the tables end here
     block_plan(d, b);
-    p.wide = nt <= ncu;
     return LBM_OK;
 }
 
@@ -1356,7 +1371,8 @@ int domain_set_tiles(lbm_domain* d, int tile_w, int tile_h) {
 bool domain_make_blocks(lbm_domain* d, int steps, Arena* pool) {
     domain_drop_blocks(d, pool);
     BlockTables b;
-    if (!domain_blockable(d) || !block_tables(d, steps, d->links, b)) return false;
+    if (!domain_blockable(d) || !block_tables(d, steps, kBlockThreads, d->links, b))
+        return false;
     BlockPlan& p = d->block;
     const size_t nt = (size_t)b.nstrips * b.nsegs;
     p.tiles = static_cast<BlockTile*>(pool->alloc(nt * sizeof(BlockTile)));

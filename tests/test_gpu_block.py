@@ -78,6 +78,18 @@ def test_sizes_around_a_tile(L, nx, ny, storage):
                      rho_wall=np.ones((ny, nx))), storage)
 
 
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16dev"])
+@pytest.mark.parametrize("nx,ny", [(3, 5), (8, 8), (9, 7), (23, 24), (24, 25), (100, 50),
+                                   (128, 121), (129, 129)])
+def test_small_single_phase_sizes(L, nx, ny, storage):
+    say(f"[gpu] blocks vs single steps, single phase {nx}x{ny} {storage}")
+    y, x = np.mgrid[:ny, :nx]
+    p = cfg.couette(10, rule="halfway", fix="none")
+    rho0 = 1.0 + 0.01 * np.cos(0.7 * x + 0.3) * np.sin(1.1 * y)
+    _same(L, p.with_(nx=nx, ny=ny, solid=np.zeros((ny, nx), np.uint8), links=p.links[:0],
+                     rho0=rho0, rho_wall=np.ones((ny, nx)), gravity=(1e-5, 2e-5)), storage)
+
+
 @pytest.mark.parametrize("make", [
     lambda: cfg.couette(10, rule="mls", fix="A"),              # moving walls
     lambda: cfg.cylinder_flow(20.0, fix="B", d=8.0),           # open x
