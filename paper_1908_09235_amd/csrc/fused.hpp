@@ -378,8 +378,8 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
         step(k + 2, C, A);
     }
 
-    const MassPart v1 = mass_wave_sum(mass_part(msum1.a, msum1.b, a.mass.inv));
-    const MassPart v2 = mass_wave_sum(mass_part(msum2.a, msum2.b, a.mass.inv));
+    const MassPart v1 = mass_wave_part(msum1.a, msum1.b, a.mass.inv);
+    const MassPart v2 = mass_wave_part(msum2.a, msum2.b, a.mass.inv);
     if (j == 0) {
         a.partial1[tile] = v1;
         a.partial2[tile] = v2;

@@ -27,6 +27,8 @@
 //     mass (MassPart); the next launch adds the partials.
 #pragma once
 
+#include <type_traits>
+
 #include "lattice.hpp"
 
 namespace lbm {
@@ -92,32 +94,58 @@ struct MassSum {
     }
 };
 
-// A sum of multiples and rests in integers.
-__device__ __forceinline__ MassPart mass_part(double a, double b, double inv) {
-    const double n = a * inv, r = b * inv;
-    if (!(fabs(n) < 9007199254740992.0 && fabs(r) <= 4194304.0))
-        return MassPart{0, 0, 0, a + b};
-    // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
-    const double w = rint(n);
-    const long long q = (long long)w;
-    const long long f = (long long)rint(((n - w) + r) * (1.0 / kMassFine));
-    return MassPart{q & 0xffffffffll, q >> 32, f, 0.0};
-}
 __device__ __forceinline__ void mass_take(MassPart& v, const MassPart& p) {
     v.lo += p.lo;
     v.hi += p.hi;
     v.fine += p.fine;
     v.big += p.big;
 }
+// Sum over the 64 lanes of a wavefront, in all of them: within rows of 16
+// lanes (shifts by 1, 2, 4 and 8), then the rows' last lanes onwards (row_bcast
+// 15 and 31).  Shifts of the vector unit: with shuffles through LDS, 48 of
+// them for the four parts, the end of a nine-row tile cost 1 to 3 % of a step (20
+// steps at 1500 x 1400, FP32 795 -> 768 us, FP16 per-node 744 -> 724).
+__device__ __forceinline__ long long wave_total(long long v) {
+    auto take = [&](auto ctrl, auto rows) {
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value,
+                                                   decltype(rows)::value, 0xf, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), decltype(ctrl)::value,
+                                                   decltype(rows)::value, 0xf, false);
+        v += (long long)((unsigned long long)(unsigned)hi << 32 | (unsigned)lo);
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, 0xf> all{};
+    take(integral_constant<int, 0x111>{}, all);
+    take(integral_constant<int, 0x112>{}, all);
+    take(integral_constant<int, 0x114>{}, all);
+    take(integral_constant<int, 0x118>{}, all);
+    take(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+    take(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(v >> 32), 63);
+    return (long long)((unsigned long long)hi << 32 | lo);
+}
+// (what integers do not hold: not in a stable run; in lane 0)
+__device__ __forceinline__ double wave_big(double v) {
+    if (__builtin_amdgcn_ballot_w64(!(v == 0.0)))
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    return v;
+}
 // Sum over the lanes of a wavefront, in lane 0.
-__device__ __forceinline__ MassPart mass_wave_sum(MassPart p) {
-    for (int off = 32; off > 0; off >>= 1) {
-        p.lo += __shfl_down(p.lo, off, 64);
-        p.hi += __shfl_down(p.hi, off, 64);
-        p.fine += __shfl_down(p.fine, off, 64);
-        p.big += __shfl_down(p.big, off, 64);
-    }
-    return p;
+__device__ __forceinline__ MassPart mass_wave_sum(const MassPart& p) {
+    return MassPart{wave_total(p.lo), wave_total(p.hi), wave_total(p.fine), wave_big(p.big)};
+}
+// A sum of multiples and rests in integers, over the lanes of a wavefront, in
+// lane 0 (at most 2^53 units a lane: 64 of them fit an integer as they are).
+__device__ __forceinline__ MassPart mass_wave_part(double a, double b, double inv) {
+    const double n = a * inv, r = b * inv;
+    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= 4194304.0;
+    // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
+    const double w = rint(n);
+    const long long q = wave_total(in ? (long long)w : 0ll);
+    const long long f =
+        wave_total(in ? (long long)rint(((n - w) + r) * (1.0 / kMassFine)) : 0ll);
+    return MassPart{q & 0xffffffffll, q >> 32, f, wave_big(in ? 0.0 : a + b)};
 }
 __device__ __forceinline__ double mass_value(MassPart p, double unit) {
     // carries upwards, then three exact doubles, rounded as one sum: the
@@ -539,7 +567,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
     }
 
     if constexpr (!MOMENTS) {
-        const MassPart v = mass_wave_sum(mass_part(msum.a, msum.b, a.mass.inv));
+        const MassPart v = mass_wave_part(msum.a, msum.b, a.mass.inv);
         if ((tid & 63) == 0) wsum[tid >> 6] = v;
         __syncthreads();
         if (tid == 0) {
