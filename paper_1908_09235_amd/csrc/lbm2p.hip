@@ -57,11 +57,11 @@ double block_us(const lbm_domain* d, int steps, long long tiles, int ncu, int la
     static const Cost costs[2][4] = {{{5.9, 2.1, 7.0, 0.0175, 0.0033},    // single phase: FP64
                                       {5.9, 2.1, 7.0, 0.0115, 0.0043},    // FP32, arithmetic FP64
                                       {5.4, 1.8, 7.0, 0.0135, 0.0014},    // FP32
-                                      {5.4, 1.8, 7.0, 0.0046, 0.0033}},   // FP16
+                                      {5.4, 1.8, 7.0, 0.0059, 0.0033}},   // FP16
                                      {{6.4, 2.45, 4.0, 0.0163, 0.0037},   // two phases
                                       {6.4, 2.45, 4.0, 0.0095, 0.0053},
                                       {5.0, 2.05, 2.0, 0.0115, 0.0018},
-                                      {5.0, 2.05, 2.0, 0.0046, 0.0033}}};
+                                      {5.0, 2.05, 2.0, 0.0059, 0.0033}}};
     const Cost& c = costs[two_phase][d->esize == 8                   ? 0
                                      : d->storage == LBM_STORE_F32   ? 1
                                      : d->esize == 4                 ? 2
@@ -452,10 +452,15 @@ void launch_pass(lbm_domain* d, bool two, hipEvent_t* rec) {
 }
 
 // Runs of steps go through k_block where the domain has a plan for it, also
-// with two steps per pass asked for; rows per tile asked for with them name
-// the two-step kernel.
+// with two steps per pass asked for, but for rows per tile asked for with them,
+// which name the two-step kernel, and large domains without walls, where its
+// tiles have no wall rules to wait for (free droplet, FP32, us a step in blocks
+// and in the two-step kernel: 1024^2 14.8 and 22.1, 2048^2 55.8 and 50.0, 2304 x
+// 2048 64.4 and 56.2; with walls 2048^2 52 and 85).
 bool uses_blocks(const lbm_domain* d) {
-    return d->block.steps > 0 && !(d->fused == 2 && d->tile_h2_asked);
+    if (d->block.steps == 0) return false;
+    if (d->fused != 2) return true;
+    return !d->tile_h2_asked && !(d->nl == 0 && d->fluid > 3000000);
 }
 
 // k steps in one launch of k_block, which also records the masses of the

@@ -172,3 +172,26 @@ def test_batch(L, storage, eos, runs):
         finally:
             for d in doms:
                 d.close()
+
+
+@pytest.mark.parametrize("storage", ["f32_arith32", "f32dev"])
+def test_two_steps_per_pass_without_walls(L, storage):
+    """Asked for two steps per pass, lattices without walls go through blocks
+    up to three million nodes and through the two-step kernel beyond."""
+    for nx, ny in ((1733, 1731), (1733, 1733)):
+        x = np.arange(nx)[None, :] * (2.0 * np.pi / nx)
+        y = np.arange(ny)[:, None] * (2.0 * np.pi / ny)
+        p = cfg.free_droplet(64, 16.0, eos="exp")
+        p = p.with_(nx=nx, ny=ny, solid=np.zeros((ny, nx), np.uint8), rho_wall=np.ones((ny, nx)),
+                    rho0=200.0 + np.sin(3 * x) * np.cos(2 * y))
+        say(f"[gpu] two steps per pass without walls {nx}x{ny} {storage}")
+        with L.Domain(p, storage=storage, history_capacity=64) as a, \
+                L.Domain(p, storage=storage, history_capacity=64) as b:
+            L.lbm_set_profiling(a.h, 1)
+            L.lbm_set_steps_per_pass(b.h, 2)
+            for n in (5, 2, 8):
+                a.step(n)
+                b.step(n)
+                for u, v in zip(a.moments(), b.moments()):
+                    assert np.array_equal(u, v)
+                assert np.array_equal(a.mass_history(), b.mass_history())
