@@ -257,9 +257,7 @@ BInst make_inst(lbm_domain* d) {
 int plan_batch(lbm_batch* b) {
     if (b->pool_state < 0 || b->ncu <= 0) return 0;
     // (the tables are made with waits, which a capture would not take)
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(b->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
-        return 0;
+    if (being_captured(b->stream)) return 0;
     double fluid = 0.0;
     long long tiles[kBlockSteps + 1] = {};
     const lbm_domain* any = nullptr;
@@ -453,7 +451,7 @@ int enqueue(lbm_batch* b, long long n) {
     long long done = 0;
     // n - 1 steps in launches of several, one launch without new steps for
     // instances that were held back (see block_steps), and a single step
-    if (b->block_steps > 0 && !b->tuning && n > b->block_steps) {
+    if (b->block_steps > 0 && !b->tuning && n > b->block_steps && !being_captured(b->stream)) {
         BlockBatchLaunch B{};
         B.args.inst = b->d_block;
         B.args.state = b->d_state;

@@ -168,6 +168,9 @@ long long domain_block_tiles(const lbm_domain* d, int steps, int lanes = kBlockT
 bool domain_make_blocks(lbm_domain* d, int steps, Arena* pool);
 void domain_drop_blocks(lbm_domain* d, Arena* pool);
 BlockArgs block_args(const lbm_domain* d);
+// Whether the caller is recording a stream: launches of blocks would be recorded
+// with the buffers of that call, so it goes the way of single steps.
+bool being_captured(hipStream_t stream);
 
 // Estimated time of a step in us: single steps (boundary and main launch), and
 // launches of k_block with `steps` steps on `tiles` tiles.  Fitted to measured

@@ -569,7 +569,8 @@ hipGraphExec_t step_graph(lbm_domain* d, int parity, int level) {
 int run_steps(lbm_domain* d, int64_t n) {
     reduce_pending(d);  // every run below starts with no mass pending
     if (d->prof > 0) return run_steps_profiled(d, n);
-    if (uses_blocks(d) && n > 1) {
+    const bool blocks = uses_blocks(d) && !(n > 1 && being_captured(d->stream));
+    if (blocks && n > 1) {
         // the last step is a pass of its own: it leaves f*(t - 1) with the
         // ghosts of step t and the wall force, which the read-outs use
         while (n > 1) {
@@ -592,7 +593,7 @@ int run_steps(lbm_domain* d, int64_t n) {
             // all runs for both parities at once, so that later calls of
             // any length replay without capturing
             // (with k_block only single steps come here)
-            const int levels = uses_blocks(d) ? 1 : lbm_domain::kGraphLevels;
+            const int levels = blocks ? 1 : lbm_domain::kGraphLevels;
             for (int par = 0; par < 2; ++par)
                 for (int lv = 0; lv < levels; ++lv) (void)step_graph(d, par, lv);
         }
@@ -1236,9 +1237,18 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if (d->fusable)  // and for two-step tiles down to kMinTileH2 rows
         d->partial_cap = std::max(d->partial_cap,
                                   d->nstrips2 * ((ny + kMinTileH2 - 1) / kMinTileH2));
-    if ((rc = dev_alloc(d, (void**)&d->partial,
-                        (size_t)(d->fusable ? 2 : 1) * d->partial_cap * sizeof(MassPart))))
+    const size_t pbytes = (size_t)(d->fusable ? 2 : 1) * d->partial_cap * sizeof(MassPart);
+    if (d->arena) {
+        // In an arena (batched and served instances) the read-out buffer is
+        // part of the footprint, so that reading a finished instance never
+        // fails.  The partials share its place: a step's are summed before its
+        // fields can be read.
+        if ((rc = dev_alloc(d, (void**)&d->mom_out, std::max<size_t>((size_t)3 * N * 8, pbytes))))
+            return rc;
+        d->partial = reinterpret_cast<MassPart*>(d->mom_out);
+    } else if ((rc = dev_alloc(d, (void**)&d->partial, pbytes))) {
         return rc;
+    }
     if (d->fusable) {
         if ((rc = upload(d, &d->node_link, node_link))) return rc;
         if ((rc = dev_alloc(d, (void**)&d->tile_order, (size_t)d->partial_cap * 4))) return rc;
@@ -1253,9 +1263,6 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if ((rc = dev_alloc(d, (void**)&d->hist, (size_t)d->cap * 8))) return rc;
     if ((rc = dev_alloc(d, (void**)&d->unstable, 8))) return rc;
     if ((rc = dev_alloc(d, (void**)&d->clock, 8))) return rc;
-    // in an arena (batched and served instances) the read-out buffer is part
-    // of the footprint, so that reading a finished instance never fails
-    if (d->arena && (rc = dev_alloc(d, (void**)&d->mom_out, (size_t)3 * N * 8))) return rc;
     if ((rc = upload(d, &d->lnode, lnode))) return rc;
     if ((rc = upload(d, &d->lmeta, lmeta))) return rc;
     if ((rc = upload(d, &d->lghost, lghost))) return rc;
@@ -1371,6 +1378,13 @@ int domain_set_tiles(lbm_domain* d, int tile_w, int tile_h) {
     d->nsegs = ng;
     d->nblocks = ns * ng;
     return LBM_OK;
+}
+
+bool being_captured(hipStream_t stream) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 bool domain_make_blocks(lbm_domain* d, int steps, Arena* pool) {
