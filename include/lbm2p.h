@@ -181,8 +181,8 @@ int lbm_create_domain(const lbm_desc *desc, lbm_domain **out);
  * (Eqs. 1-2, 4; MRT as in Sec. 3.2), the pull streaming (Eq. 3), the rule
  * of every cut link (Eqs. 6-14), the correction at every boundary node
  * (Eqs. 15, 17-23) and the total mass.  Steps are enqueued on the domain's
- * stream (as HIP graph replays once the step count repeats) and no host
- * data moves.  n = 0 does nothing.  LBM_EUNSTABLE names the first step
+ * stream (several to a launch, or as HIP graph replays) and no host data
+ * moves.  n = 0 does nothing.  LBM_EUNSTABLE names the first step
  * whose total mass was not finite (see lbm_unstable_step); further steps
  * still run on the non-finite state and report the same first step. */
 int lbm_step(lbm_domain *d, int64_t n);
