@@ -242,16 +242,16 @@ BInst make_inst(lbm_domain* d) {
 // k_block costs less here than in one large lattice (see block_us), whose
 // nodes are all fluid and leave the last cache between launches.  Measured, us
 // a step, single / 2 / 3 / 4 steps per launch:
-//   6 sessile droplets 400 x 200, FP64           41.3 / 18.8 / 17.9 / 21.2
-//   3 droplets of sides 64 to 128, FP64          37.5 /  8.6 /  7.1 /  6.2
-//   12 of sides 64 to 768 (2.8 M nodes), FP64    98.9 / 71.5 / 72.9 / 91.6
-//     FP32 storage, FP64 arithmetic              66.2 / 60.0 / 70.7 / 90.9
-//     FP32 arithmetic                            56.3 / 36.2 / 40.3 / 50.6
-//     FP16 deviations                            52.3 / 41.3 / 46.4 / 58.2
-//   24 of sides 200 to 768 (6.1 M nodes), FP64  202.9 / 145.6 / 147.7 / 190.6
-//     FP32 storage, FP64 arithmetic             116.0 / 124.4 / 144.0 / 188.8
-//     FP32 arithmetic                           109.2 / 83.7 / 84.1 / 105.8
-//     FP16 deviations                            76.0 / 85.7 / 93.5 / 121.6
+//   6 sessile droplets 400 x 200, FP64           40.4 / 17.4 / 16.5 / 19.4
+//   3 droplets of sides 64 to 128, FP64          36.9 /  7.7 /  6.5 /  5.7
+//   12 of sides 64 to 768 (2.8 M nodes), FP64    97.8 / 66.0 / 66.2 / 83.1
+//     FP32 storage, FP64 arithmetic              65.5 / 52.3 / 62.7 / 82.2
+//     FP32 arithmetic                            55.5 / 33.1 / 35.8 / 44.1
+//     FP16 deviations                            51.6 / 35.7 / 40.2 / 49.9
+//   24 of sides 200 to 768 (6.1 M nodes), FP64  204.1 / 134.3 / 134.0 / 172.2
+//     FP32 storage, FP64 arithmetic             116.1 / 109.7 / 127.9 / 172.0
+//     FP32 arithmetic                           108.6 / 78.4 / 77.2 / 93.6
+//     FP16 deviations                            75.1 / 72.9 / 79.4 / 102.8
 // The choice changes only when that gains a tenth, since every instance's
 // tables are made again.
 int plan_batch(lbm_batch* b) {
@@ -274,7 +274,7 @@ int plan_batch(lbm_batch* b) {
     if (!any) return 0;
     double best = 28.0 + 18.0 * (double)any->esize * fluid * 1e-6 / 5.2;
     int steps = 0;
-    const double part = any->esize == 2 ? 1.05 : 0.9;
+    const double part = 0.82;
     auto cost = [&](int k) {  // (and the reduction's launch)
         const long long more = std::max<long long>(tiles[k] - b->ncu, 0);
         return block_us(any, k, std::min<long long>(tiles[k], b->ncu) + (long long)(part * more),
