@@ -296,12 +296,15 @@ int make_blocks(lbm_batch* b) {
     b->nbtiles = 0;
     b->block_lds = 0;
     if (b->block_steps == 0) return LBM_OK;
+    auto single = [&] {
+        b->block_steps = 0;
+        (void)hipGetLastError();
+        return (int)LBM_OK;
+    };
     for (lbm_domain* d : b->inst)
         if (d && d->block.steps != b->block_steps &&
-            !domain_make_blocks(d, b->block_steps, &b->pool)) {
-            b->block_steps = 0;
-            return LBM_OK;
-        }
+            !domain_make_blocks(d, b->block_steps, &b->pool))
+            return single();
     for (const lbm_domain* d : b->inst)
         if (d) {
             b->nbtiles += d->block.ntiles;
@@ -314,7 +317,7 @@ int make_blocks(lbm_batch* b) {
         b->d_btiles = nullptr;
         b->h_btiles = nullptr;
         b->btiles_cap = 0;
-        if (dmalloc(&b->d_btiles, cap) || hmalloc(&b->h_btiles, cap)) return LBM_ENOMEM;
+        if (dmalloc(&b->d_btiles, cap) || hmalloc(&b->h_btiles, cap)) return single();
         b->btiles_cap = cap;
     }
     int n = (int)b->inst.size();
@@ -327,7 +330,7 @@ int make_blocks(lbm_batch* b) {
         b->d_block = nullptr;
         b->h_block = nullptr;
         b->block_cap = 0;
-        if (dmalloc(&b->d_block, cap) || hmalloc(&b->h_block, cap)) return LBM_ENOMEM;
+        if (dmalloc(&b->d_block, cap) || hmalloc(&b->h_block, cap)) return single();
         b->block_cap = cap;
     }
     long long k = 0;

@@ -819,6 +819,16 @@ bool block_tables(const lbm_domain* d, int steps, int lanes, const LinkTables& l
     return true;
 }
 
+// (no tables either where the host has no memory for them)
+bool try_block_tables(const lbm_domain* d, int steps, int lanes, const LinkTables& lt,
+                      BlockTables& b) {
+    try {
+        return block_tables(d, steps, lanes, lt, b);
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+}
+
 // Whether and how the domain's runs go through k_block: the number of steps
 // per launch with the least estimated time, if that is below single steps'.
 int plan_blocks(lbm_domain* d, const LinkTables& lt) {
@@ -843,16 +853,37 @@ int plan_blocks(lbm_domain* d, const LinkTables& lt) {
             }
         }
     BlockTables b;
-    if (steps == 0 || !block_tables(d, steps, lanes, lt, b)) return LBM_OK;
+    if (steps == 0 || !try_block_tables(d, steps, lanes, lt, b)) return LBM_OK;
     BlockPlan& p = d->block;
-    int rc;
-    if ((rc = upload(d, &p.tiles, b.tiles)) || (rc = upload(d, &p.links, b.links)) ||
-        (rc = upload(d, &p.nodes, b.nodes)))
-        return rc;
-    const int nt = b.nstrips * b.nsegs;
-    for (MassPart*& q : p.partial)
-        if ((rc = dev_alloc(d, (void**)&q, (size_t)steps * nt * sizeof(MassPart)))) return rc;
-    if (hipStreamSynchronize(d->stream) != hipSuccess) return LBM_EDEVICE;  // the tables end here
+    const size_t tiles = b.tiles.size() * sizeof(BlockTile);
+    const size_t links = b.links.size() * sizeof(BlockLink);
+    const size_t nodes = b.nodes.size() * sizeof(BlockNode);
+    const size_t part = (size_t)steps * b.tiles.size() * sizeof(MassPart);
+    // one piece of memory; a domain that leaves no room for it takes single steps
+    char* m = nullptr;
+    auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
+    const int rc = dev_alloc(d, (void**)&m, up(tiles) + up(links) + up(nodes) + 2 * up(part));
+    if (rc) {
+        (void)hipGetLastError();
+        return LBM_OK;
+    }
+    auto place = [&](auto*& q, size_t n) {
+        q = reinterpret_cast<std::remove_reference_t<decltype(q)>>(m);
+        m += up(n);
+    };
+    place(p.tiles, tiles);
+    place(p.links, links);
+    place(p.nodes, nodes);
+    place(p.partial[0], part);
+    place(p.partial[1], part);
+    auto put = [&](void* dst, const void* src, size_t n) {
+        return n == 0 ||
+               hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, d->stream) == hipSuccess;
+    };
+    if (!put(p.tiles, b.tiles.data(), tiles) || !put(p.links, b.links.data(), links) ||
+        !put(p.nodes, b.nodes.data(), nodes) ||
+        hipStreamSynchronize(d->stream) != hipSuccess)  // the tables end here
+        return LBM_EDEVICE;
     block_plan(d, b);
     return LBM_OK;
 }
@@ -1390,7 +1421,7 @@ bool being_captured(hipStream_t stream) {
 bool domain_make_blocks(lbm_domain* d, int steps, Arena* pool) {
     domain_drop_blocks(d, pool);
     BlockTables b;
-    if (!domain_blockable(d) || !block_tables(d, steps, kBlockThreads, d->links, b))
+    if (!domain_blockable(d) || !try_block_tables(d, steps, kBlockThreads, d->links, b))
         return false;
     BlockPlan& p = d->block;
     const size_t nt = (size_t)b.nstrips * b.nsegs;
