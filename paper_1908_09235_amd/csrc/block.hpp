@@ -518,7 +518,9 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         }
         double big = 0.0;
         for (int w = 0; w < NW; ++w) big += mbig[t][w];
-        a.partial[(long long)t * a.ntiles + tile] = MassPart{q & 0xffffffffll, q >> 32, fine, big};
+        MassPart v{q & 0xffffffffll, q >> 32, fine, big};
+        mass_carry(v);
+        a.partial[(long long)t * a.ntiles + tile] = v;
     }
 }
 

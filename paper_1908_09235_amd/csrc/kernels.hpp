@@ -67,6 +67,16 @@ struct MassPart {
     long long fine;    // of 2^-40 units (kMassFine)
     double big;        // what integers do not hold
 };
+// Carries upwards.  The rests of a domain at rest all have one sign, up to 2^39
+// of 2^-40 units each, and 2^24 of them leave 63 bits: a part is carried when
+// it is formed and when a lane has added its share, so that sums of 2^22 parts
+// stay within them (2^31 nodes and more).
+__device__ __forceinline__ void mass_carry(MassPart& v) {
+    v.lo += v.fine >> 40;
+    v.fine &= 0xffffffffffll;
+    v.hi += v.lo >> 32;
+    v.lo &= 0xffffffffll;
+}
 // Rows one lane adds up at most: 2^51 units each, in 63 bits.  A tile of more
 // rows runs as several.
 constexpr int kMassRows = 2048;
@@ -139,21 +149,23 @@ __device__ __forceinline__ MassPart mass_wave_sum(const MassPart& p) {
 // lane 0 (at most 2^53 units a lane: 64 of them fit an integer as they are).
 __device__ __forceinline__ MassPart mass_wave_part(double a, double b, double inv) {
     const double n = a * inv, r = b * inv;
-    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= 4194304.0;
+    // (the rests of kMassRows nodes, half a unit each: 64 lanes of them hold)
+    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= 0.5 * kMassRows;
     // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
     const double w = rint(n);
     const long long q = wave_total(in ? (long long)w : 0ll);
     const long long f =
         wave_total(in ? (long long)rint(((n - w) + r) * (1.0 / kMassFine)) : 0ll);
-    return MassPart{q & 0xffffffffll, q >> 32, f, wave_big(in ? 0.0 : a + b)};
+    MassPart v{q & 0xffffffffll, q >> 32, f, wave_big(in ? 0.0 : a + b)};
+    mass_carry(v);
+    return v;
 }
 __device__ __forceinline__ double mass_value(MassPart p, double unit) {
-    // carries upwards, then three exact doubles, rounded as one sum: the
-    // lowest part decides only how the sum of the others rounds
-    const long long lo = p.lo + (p.fine >> 40);
-    const long long hi = p.hi + (lo >> 32);
-    const double l = double(lo & 0xffffffffll), f = double(p.fine & 0xffffffffffll);
-    const double h = double(hi) * 4294967296.0;
+    // three exact doubles, rounded as one sum: the lowest part decides only how
+    // the sum of the others rounds
+    mass_carry(p);
+    const double l = double(p.lo), f = double(p.fine);
+    const double h = double(p.hi) * 4294967296.0;
     const double s = h + l, e = l - (s - h);  // h + l = s + e
     return (s + fma(f, kMassFine, e)) * unit + p.big;
 }
@@ -597,6 +609,7 @@ __device__ __forceinline__ MassPart sum_partials(const MassPart* __restrict__ pa
         for (int j = 0; j < 4; ++j) mass_take(v, q[j]);
     }
     for (; i < np; i += lanes) mass_take(v, partial[i]);
+    mass_carry(v);
     return v;
 }
 

@@ -1,0 +1,66 @@
+"""The total mass against the sum of the densities that lbm_moments reads out,
+added as rational numbers: a step's mass is that sum, rounded.  Domains of more
+than 2^24 nodes whose densities all leave the same rest over the unit of the
+sums, which is where the sum of the rests is largest."""
+import sys
+from fractions import Fraction
+
+import numpy as np
+import pytest
+
+from lbm_inputs import configs as cfg
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def L():
+    from paper_1908_09235_amd import lbm
+    lbm.lib()
+    return lbm
+
+
+def _still(nx, ny, rho0):
+    """A fluid without walls or forces, at rest but for the density given."""
+    return cfg.couette(10, rule="halfway", fix="none").with_(
+        nx=nx, ny=ny, solid=np.zeros((ny, nx), np.uint8),
+        links=cfg.couette(10).links[:0], rho0=rho0, rho_wall=np.ones((ny, nx)),
+        name=f"still_{nx}x{ny}")
+
+
+def _sum(rho):
+    v, n = np.unique(rho, return_counts=True)
+    return sum((Fraction(float(x)) * int(k) for x, k in zip(v, n)), Fraction(0))
+
+
+def _close(got, want):
+    """Rounded once, and the sum of the three parts it is rounded from again."""
+    ulp = np.spacing(abs(float(want)))
+    return abs(Fraction(float(got)) - want) <= Fraction(float(ulp))
+
+
+@pytest.mark.parametrize("rest", [0.44, -0.44])
+@pytest.mark.parametrize("form", ["single steps", "blocks"])
+def test_rests_of_one_sign(L, form, rest):
+    # the unit is 2^-40 of the power of two above the largest density
+    nx, ny = 4480, 4481
+    assert abs(rest) * nx * ny > 2 ** 23
+    p = _still(nx, ny, np.full((ny, nx), 0.75 + rest * 2.0 ** -40))
+    say(f"[gpu] mass of {nx}x{ny} equal densities, rest {rest} units, {form}")
+    with L.Domain(p, storage="f64", history_capacity=64) as d:
+        if form == "single steps":
+            L.lbm_set_profiling(d.h, 1)
+        for n in (0, 1, 7):
+            if n:
+                d.step(n)
+            want = _sum(d.moments()[0])
+            got = d.total_mass()
+            say(f"    t = {d.t}: off by {float(Fraction(got) - want)!r}")
+            assert _close(got, want)
+        for m in d.mass_history():
+            assert abs(m - float(want)) <= 1e-13 * float(want)
