@@ -489,7 +489,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
                                 __builtin_bit_cast(long long, mass.magic);
             const long long fn = __builtin_bit_cast(long long, z) -
                                  __builtin_bit_cast(long long, mass.magic * kMassFine);
-            if (in && q != 0) {
+            if (in && (q | fn) != 0) {
                 atomicAdd(&mq[s - 1][t % kBlockBins], (unsigned long long)q);
                 atomicAdd(&mfine[s - 1][t % kBlockBins], (unsigned long long)fn);
             }

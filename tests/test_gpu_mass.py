@@ -1,7 +1,8 @@
 """The total mass against the sum of the densities that lbm_moments reads out,
 added as rational numbers: a step's mass is that sum, rounded.  Domains of more
 than 2^24 nodes whose densities all leave the same rest over the unit of the
-sums, which is where the sum of the rests is largest."""
+sums, which is where the sum of the rests is largest; and densities far below
+the unit."""
 import sys
 from fractions import Fraction
 
@@ -64,3 +65,24 @@ def test_rests_of_one_sign(L, form, rest):
             assert _close(got, want)
         for m in d.mass_history():
             assert abs(m - float(want)) <= 1e-13 * float(want)
+
+
+def test_densities_below_the_unit(L):
+    # e-folds over four nodes from 1 in the middle down to 2^-42, an eighth of
+    # the unit, which most nodes have
+    n = 400
+    y, x = np.mgrid[:n, :n] - n // 2
+    p = _still(n, n, np.maximum(np.exp(-np.hypot(x, y) / 4.0), 2.0 ** -42))
+    say(f"[gpu] mass of {n}x{n} densities from 1 to 2^-42")
+    with L.Domain(p, storage="f64", history_capacity=64) as a, \
+            L.Domain(p, storage="f64", history_capacity=64) as b:
+        L.lbm_set_profiling(b.h, 1)  # single steps
+        a.step(10)                   # nine of them in launches of several
+        for k, got in enumerate(a.mass_history()):
+            want = _sum(b.moments()[0])
+            alone = b.total_mass()
+            say(f"    t = {k}: off by {float(Fraction(got) - want)!r}, single steps "
+                f"{float(Fraction(alone) - want)!r} of {got!r}")
+            assert np.isfinite(got) and _close(got, want) and _close(alone, want)
+            assert got == alone
+            b.step(1)
