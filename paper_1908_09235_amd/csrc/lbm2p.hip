@@ -893,8 +893,9 @@ MassUnit mass_unit(const lbm_desc* s, long long n) {
     double mx = 0.0;
     for (long long i = 0; i < n; ++i)
         if (!s->solid[i] && s->rho0[i] > mx) mx = s->rho0[i];
-    // (a range in which neither the unit nor its multiples leave FP64)
-    mx = std::min(std::max(mx, 1e-200), 1e200);
+    // (a range in which neither the unit nor its inverse leaves FP64; smaller
+    // densities are rests, down to the smallest normal numbers)
+    mx = std::min(std::max(mx, std::ldexp(1.0, -980)), 1e200);
     int e = 0;
     (void)std::frexp(mx, &e);  // mx < 2^e
     const double unit = std::ldexp(1.0, e - 40);

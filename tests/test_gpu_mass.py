@@ -86,3 +86,17 @@ def test_densities_below_the_unit(L):
             assert np.isfinite(got) and _close(got, want) and _close(alone, want)
             assert got == alone
             b.step(1)
+
+
+@pytest.mark.parametrize("rho", [3e-150, 3e-250, 1.3e-290, 3e-304, 3e200])
+def test_densities_of_any_size(L, rho):
+    n = 64
+    p = _still(n, n, np.full((n, n), rho))
+    say(f"[gpu] mass of {n}x{n} densities of {rho!r}")
+    with L.Domain(p, storage="f64", history_capacity=64) as d:
+        for k in (0, 1, 9):
+            if k:
+                d.step(k)
+            want = _sum(d.moments()[0])
+            say(f"    t = {d.t}: {d.total_mass()!r}, {float(want)!r}")
+            assert _close(d.total_mass(), want)
