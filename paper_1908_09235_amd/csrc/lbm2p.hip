@@ -830,8 +830,9 @@ bool try_block_tables(const lbm_domain* d, int steps, int lanes, const LinkTable
 }
 
 // Whether and how the domain's runs go through k_block: the number of steps
-// per launch with the least estimated time, if that is below single steps'.
-int plan_blocks(lbm_domain* d, const LinkTables& lt) {
+// per launch with the least estimated time, if that is below single steps'
+// (the tables of none otherwise).
+int plan_blocks(lbm_domain* d, const LinkTables& lt, BlockTables& b) {
     if (d->arena || !domain_blockable(d)) return LBM_OK;
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -852,17 +853,28 @@ int plan_blocks(lbm_domain* d, const LinkTables& lt) {
                 lanes = w;
             }
         }
-    BlockTables b;
-    if (steps == 0 || !try_block_tables(d, steps, lanes, lt, b)) return LBM_OK;
+    if (steps > 0 && !try_block_tables(d, steps, lanes, lt, b)) b.steps = 0;
+    return LBM_OK;
+}
+
+// The tables on the device, and moments of its own for each buffer (a launch
+// reads those of one time and writes those of another; single steps write
+// in place).  Last in the creation, when the initial fields have been given
+// back, so that a plan takes no memory that the rest of it needs.  The caller
+// waits for the stream before b ends.
+int place_blocks(lbm_domain* d, const BlockTables& b) {
+    if (b.steps == 0) return LBM_OK;
     BlockPlan& p = d->block;
     const size_t tiles = b.tiles.size() * sizeof(BlockTile);
     const size_t links = b.links.size() * sizeof(BlockLink);
     const size_t nodes = b.nodes.size() * sizeof(BlockNode);
-    const size_t part = (size_t)steps * b.tiles.size() * sizeof(MassPart);
+    const size_t part = (size_t)b.steps * b.tiles.size() * sizeof(MassPart);
+    const size_t mom = (size_t)3 * std::max(d->nslots, 1) * 8;
     // one piece of memory; a domain that leaves no room for it takes single steps
     char* m = nullptr;
     auto up = [](size_t n) { return (n + 255) & ~size_t(255); };
-    const int rc = dev_alloc(d, (void**)&m, up(tiles) + up(links) + up(nodes) + 2 * up(part));
+    const int rc =
+        dev_alloc(d, (void**)&m, up(tiles) + up(links) + up(nodes) + 2 * up(part) + up(mom));
     if (rc) {
         (void)hipGetLastError();
         return LBM_OK;
@@ -876,13 +888,13 @@ int plan_blocks(lbm_domain* d, const LinkTables& lt) {
     place(p.nodes, nodes);
     place(p.partial[0], part);
     place(p.partial[1], part);
+    place(d->side_mom[1], mom);
     auto put = [&](void* dst, const void* src, size_t n) {
         return n == 0 ||
                hipMemcpyAsync(dst, src, n, hipMemcpyHostToDevice, d->stream) == hipSuccess;
     };
     if (!put(p.tiles, b.tiles.data(), tiles) || !put(p.links, b.links.data(), links) ||
-        !put(p.nodes, b.nodes.data(), nodes) ||
-        hipStreamSynchronize(d->stream) != hipSuccess)  // the tables end here
+        !put(p.nodes, b.nodes.data(), nodes))
         return LBM_EDEVICE;
     block_plan(d, b);
     return LBM_OK;
@@ -1256,11 +1268,9 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if ((rc = upload(d, &d->flags, flags))) return rc;
     if ((rc = upload(d, &d->side_idx, side_idx))) return rc;
     if (d->esize == 2 && (rc = dev_alloc(d, (void**)&d->psiw, (size_t)P * ny * 4))) return rc;
-    // (the passes of a batch write the moments in place)
-    for (int k = 0; k < (d->arena ? 1 : 2); ++k)
-        if ((rc = dev_alloc(d, (void**)&d->side_mom[k], (size_t)3 * std::max(nslots, 1) * 8)))
-            return rc;
-    if (d->arena) d->side_mom[1] = d->side_mom[0];
+    if ((rc = dev_alloc(d, (void**)&d->side_mom[0], (size_t)3 * std::max(nslots, 1) * 8)))
+        return rc;
+    d->side_mom[1] = d->side_mom[0];  // (see place_blocks)
     if ((rc = dev_alloc(d, (void**)&d->side_f,
                         (size_t)9 * (d->save_f ? std::max(nslots, 1) : 1) * 8)))
         return rc;
@@ -1307,7 +1317,8 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if (!lref.empty() && (rc = upload(d, &d->lref, lref))) return rc;
     LinkTables lt{std::move(lnode), std::move(lmeta), std::move(lslotb), std::move(lslotf),
                   std::move(lc)};
-    if ((rc = plan_blocks(d, lt))) return rc;
+    BlockTables blocks;
+    if ((rc = plan_blocks(d, lt, blocks))) return rc;
     if (d->arena && domain_blockable(d)) d->links = lt;  // (see domain_make_blocks)
     if ((rc = dev_alloc(d, (void**)&d->force,
                         (size_t)2 * std::max(link_blocks(d), 1) * 8)))
@@ -1372,6 +1383,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if (hipStreamSynchronize(d->stream) != hipSuccess) return LBM_EDEVICE;
     // the initial fields are no longer needed
     for (double* p : {drw, dr0, du0, dv0}) dev_free(d, p, (size_t)N * 8);
+    if ((rc = place_blocks(d, blocks))) return rc;
     return check_unstable(d);
 }
 
