@@ -243,7 +243,11 @@ int lbm_set_state(lbm_domain *d, const void *buf, size_t bytes);
  * domain's stream (the dispatch's timestamps, as a kernel profiler reads
  * them; no host synchronisation until 1024 samples are pending);
  * lbm_kernel_times returns the summed durations (ms) and sample counts
- * since profiling was last set.  every = 0 switches it off. */
+ * since profiling was last set.  every = 0 switches it off.  While it is
+ * on, every pass is a boundary and a main launch of one step (or of two, see
+ * lbm_set_steps_per_pass): runs do not keep more steps on chip
+ * (lbm_get_blocks), so they last as long as these launches, not as long as the
+ * same runs without timing.  The results are the same. */
 int lbm_set_profiling(lbm_domain *d, int every);
 int lbm_kernel_times(lbm_domain *d, double *main_ms, int64_t *main_count,
                      double *boundary_ms, int64_t *boundary_count);
@@ -308,6 +312,12 @@ int lbm_degenerate_b(lbm_domain *d, int64_t *count);
  * (x_f or x_ff solid) taken per step. */
 int lbm_info(lbm_domain *d, int64_t out[8]);
 
+/* How runs of more than one step are launched under the domain's present
+ * settings: out[0] steps a launch makes on blocks of the lattice held on
+ * chip, or 0 where every launch is a pass of one or two steps (no gain, or no
+ * room for the tables, or kernels being timed); then out[1] lanes per
+ * block and out[2] blocks (0, 0). */
+int lbm_get_blocks(lbm_domain *d, int32_t out[3]);
 void lbm_destroy(lbm_domain *d);
 const char *lbm_status_string(int status);
 
@@ -389,6 +399,9 @@ int lbm_batch_tune(lbm_batch *b, int64_t steps_per_trial, int32_t out[5]);
 /* [0] instances, [1] main-pass tiles, [2] link blocks, [3] arena bytes,
  * [4] arena bytes in use, [5] tile_w, [6] tile_h, [7] persistent. */
 int lbm_batch_info(lbm_batch *b, int64_t out[8]);
+/* As lbm_get_blocks, for the instances of the last lbm_batch_run (0, 0, 0
+ * before one). */
+int lbm_batch_get_blocks(lbm_batch *b, int32_t out[3]);
 void lbm_batch_destroy(lbm_batch *b);
 
 /* ------------------------------------------------------------------------

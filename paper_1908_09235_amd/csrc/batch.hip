@@ -802,6 +802,14 @@ int lbm_batch_info(lbm_batch* b, int64_t out[8]) {
     return LBM_OK;
 }
 
+int lbm_batch_get_blocks(lbm_batch* b, int32_t out[3]) {
+    if (!b || !out) return LBM_EINVAL;
+    out[0] = b->block_steps;
+    out[1] = b->block_steps ? kBlockThreads : 0;
+    out[2] = b->block_steps ? (int32_t)b->nbtiles : 0;
+    return LBM_OK;
+}
+
 void lbm_batch_destroy(lbm_batch* b) { free_batch(b); }
 
 // ------------------------------------------------------------------ server

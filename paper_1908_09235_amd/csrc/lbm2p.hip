@@ -1932,6 +1932,15 @@ int lbm_info(lbm_domain* d, int64_t out[8]) {
     return LBM_OK;
 }
 
+int lbm_get_blocks(lbm_domain* d, int32_t out[3]) {
+    if (!d || !out) return LBM_EINVAL;
+    const bool on = uses_blocks(d) && d->prof == 0;
+    out[0] = on ? d->block.steps : 0;
+    out[1] = on ? d->block.lanes : 0;
+    out[2] = on ? d->block.ntiles : 0;
+    return LBM_OK;
+}
+
 void lbm_destroy(lbm_domain* d) {
     if (!d) return;
     (void)hipStreamSynchronize(d->stream);

@@ -86,6 +86,7 @@ EXPORTS = {
     "lbm_kernel_times": (C.c_int, [_H, _D, C.POINTER(C.c_int64), _D,
                                    C.POINTER(C.c_int64)]),
     "lbm_info": (C.c_int, [_H, C.POINTER(C.c_int64)]),
+    "lbm_get_blocks": (C.c_int, [_H, C.POINTER(C.c_int32)]),
     "lbm_set_steps_per_pass": (C.c_int, [_H, C.c_int32, C.c_int32]),
     "lbm_get_steps_per_pass": (C.c_int, [_H, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
     "lbm_tune_steps_per_pass": (C.c_int, [_H, C.c_int64, C.POINTER(C.c_int32)]),
@@ -105,6 +106,7 @@ EXPORTS = {
     "lbm_batch_remove": (C.c_int, [_H, C.c_int32]),
     "lbm_batch_tune": (C.c_int, [_H, C.c_int64, C.POINTER(C.c_int32)]),
     "lbm_batch_info": (C.c_int, [_H, C.POINTER(C.c_int64)]),
+    "lbm_batch_get_blocks": (C.c_int, [_H, C.POINTER(C.c_int32)]),
     "lbm_batch_destroy": (None, [_H]),
     "lbm_server_create": (C.c_int, [C.POINTER(lbm_batch_desc), C.c_int64, C.POINTER(_H)]),
     "lbm_server_submit": (C.c_int, [_H, C.POINTER(lbm_desc), C.c_int64,
@@ -306,6 +308,13 @@ def lbm_info(h):
     return dict(zip(keys, list(out)))
 
 
+def lbm_get_blocks(h):
+    """Steps per launch on blocks (0: none), lanes per block, blocks."""
+    out = (C.c_int32 * 3)()
+    _check(lib().lbm_get_blocks(h, out), "lbm_get_blocks")
+    return tuple(out)
+
+
 def lbm_destroy(h):
     lib().lbm_destroy(h)
 
@@ -367,6 +376,9 @@ class Domain:
 
     def info(self):
         return lbm_info(self.h)
+
+    def blocks(self):
+        return lbm_get_blocks(self.h)
 
     def negative_rest(self):
         return lbm_negative_rest(self.h)
@@ -475,6 +487,12 @@ def lbm_batch_info(h):
     return dict(zip(keys, list(out)))
 
 
+def lbm_batch_get_blocks(h):
+    out = (C.c_int32 * 3)()
+    _check(lib().lbm_batch_get_blocks(h, out), "lbm_batch_get_blocks")
+    return tuple(out)
+
+
 def lbm_batch_destroy(h):
     lib().lbm_batch_destroy(h)
 
@@ -518,6 +536,9 @@ class Batch:
 
     def info(self):
         return lbm_batch_info(self.h)
+
+    def blocks(self):
+        return lbm_batch_get_blocks(self.h)
 
     def close(self):
         if getattr(self, "h", None) is not None and self.h.value:
