@@ -1835,10 +1835,10 @@ int lbm_set_steps_per_pass(lbm_domain* d, int32_t steps, int32_t tile_h) {
     if (steps == 2 && !d->fusable) return LBM_EINVAL;
     const int th = tile_h ? tile_h : kTileH2;
     if (steps == 2) {
-        d->tile_h2_asked = tile_h > 0;
         if (th < kMinTileH2) return LBM_EINVAL;
         const int ng = seg_count(d->ny, th);
         if ((long long)d->nstrips2 * ng > d->partial_cap) return LBM_EINVAL;
+        d->tile_h2_asked = tile_h > 0;
         d->tile_h2 = th;
         d->nsegs2 = ng;
         d->nblocks2 = d->nstrips2 * ng;
@@ -1874,6 +1874,7 @@ int lbm_tune_steps_per_pass(lbm_domain* d, int64_t steps_per_trial, int32_t out[
     }
     // whole runs are timed, so the steps replay their graphs as lbm_step does
     const int prof = d->prof, steps0 = d->fused, tile0 = d->tile_h2;
+    const bool asked0 = d->tile_h2_asked;
     d->prof = 0;
     int rc = LBM_OK;
     float best = 0.0f;
@@ -1900,6 +1901,7 @@ int lbm_tune_steps_per_pass(lbm_domain* d, int64_t steps_per_trial, int32_t out[
     if (rc) {
         // the caller's setting again (it was valid when set)
         (void)lbm_set_steps_per_pass(d, steps0, steps0 == 2 ? tile0 : 0);
+        d->tile_h2_asked = asked0;
         return rc;
     }
     if ((rc = lbm_set_steps_per_pass(d, pick.steps, pick.tile_h))) return rc;

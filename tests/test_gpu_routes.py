@@ -115,6 +115,18 @@ def test_no_blocks_where_single_steps_are_meant(L):
         assert d.blocks() == on
 
 
+def test_a_refused_setting_changes_nothing(L):
+    with L.Domain(_drop("mls", "A"), storage="f32", history_capacity=16) as d:
+        for tile_h in (0, 16):
+            L.lbm_set_steps_per_pass(d.h, 2, tile_h)
+            setting, on = L.lbm_get_steps_per_pass(d.h), d.blocks()
+            assert (on[0] >= 2) == (tile_h == 0)
+            for steps, refused in ((2, 3), (2, -1), (3, 0), (1, -1)):
+                assert L.lib().lbm_set_steps_per_pass(d.h, steps, refused) == L.LBM_EINVAL
+                assert L.lbm_get_steps_per_pass(d.h) == setting
+                assert d.blocks() == on, (steps, refused)
+
+
 def test_tables_that_do_not_fit_a_block(L):
     """With a third of the nodes solid a block of 32 x 32 has more links than a
     workgroup has lanes."""
