@@ -91,7 +91,7 @@ struct BlockArgs {
     double* mom[2];                        // side moments of the times of f[0], f[1]
     const uint8_t* flags;
     const float* psiw;                     // FP16 storage: psi_w of solid nodes
-    MassPart* partial;                     // [step][tile]
+    MassTile* partial;                     // [step][tile]
     const BlockTile* tiles;
     const BlockLink* links;
     const BlockNode* nodes;
@@ -440,7 +440,6 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         MassSum<SPLIT> msum;
         MassUnit mass;
         mass.magic = a.mass.magic;
-        mass.unit = a.mass.unit;
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
             const int n = t + j * NT;
@@ -484,7 +483,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
             const double x = msum.a + mass.magic;
             const double y = msum.b + (SPLIT ? 0.0 : msum.a - (x - mass.magic));
             const double z = y + mass.magic * kMassFine;
-            const bool in = fabs(msum.a) < mass.unit * 1125899906842624.0;  // 2^50 units
+            const bool in = fabs(msum.a) < 0.25 * mass.magic;  // 1.5 * 2^50 units
             const long long q = __builtin_bit_cast(long long, x) -
                                 __builtin_bit_cast(long long, mass.magic);
             const long long fn = __builtin_bit_cast(long long, z) -
@@ -518,9 +517,8 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         }
         double big = 0.0;
         for (int w = 0; w < NW; ++w) big += mbig[t][w];
-        MassPart v{q & 0xffffffffll, q >> 32, fine, big};
-        mass_carry(v);
-        a.partial[(long long)t * a.ntiles + tile] = v;
+        a.partial[(long long)t * a.ntiles + tile] =
+            mass_pack(MassPart{q & 0xffffffffll, q >> 32, fine, big}, mass_unit(a.mass.magic));
     }
 }
 
@@ -537,7 +535,7 @@ template <typename S, typename R, int EOS, int DEV, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(block_waves<R>(NT)))) void
 k_block(BlockKernarg k) {
     if ((int)blockIdx.x == (int)gridDim.x - 1) {
-        if (k.r.do_reduce) reduce_pass(k.r.prev);
+        if (k.r.do_reduce) reduce_pass<8>(k.r.prev);
         return;
     }
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -589,7 +587,7 @@ __global__ __launch_bounds__(256) void k_block_reduce(BlockBatch b) {
         const int n = block_steps(st->remaining, st->hold, b.steps);
         if (n <= 0) continue;
         const auto& I = ro(b.inst)[i];
-        sum_masses(I.partial, I.ntiles, n, I.ntiles, I.mass.unit,
+        sum_masses<16>(I.partial, I.ntiles, n, I.ntiles, mass_unit(I.mass.magic),
                    [&](int s, double v) { m[s] = v; });
         if (threadIdx.x == 0) {
             int bad = 0;

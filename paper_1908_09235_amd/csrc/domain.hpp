@@ -49,7 +49,7 @@ struct BlockPlan {
     BlockTile* tiles = nullptr;
     BlockLink* links = nullptr;
     BlockNode* nodes = nullptr;
-    MassPart* partial[2] = {nullptr, nullptr};  // [step][tile], used in turn
+    MassTile* partial[2] = {nullptr, nullptr};  // [step][tile], used in turn
     int set = 0;                                // the one written last
 };
 
@@ -79,7 +79,7 @@ struct lbm_domain {
     int nslots = 0;
     bool save_f = false;
     // mass partials of the last pass: one array of partial_cap per step
-    lbm::MassPart* partial = nullptr;
+    lbm::MassTile* partial = nullptr;
     lbm::MassUnit mass{};
     double* hist = nullptr;
     long long* unstable = nullptr;

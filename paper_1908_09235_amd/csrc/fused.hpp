@@ -45,8 +45,8 @@ struct Main2Args {
     const int* __restrict__ order;        // tile of each workgroup (null: XCD order)
     const float* __restrict__ psiw;       // FP16 storage: psi_w of solid nodes
     double* __restrict__ side_mom;        // moments of t + 2 of flagged nodes
-    MassPart* __restrict__ partial1;      // per workgroup: mass at t + 1
-    MassPart* __restrict__ partial2;      // per workgroup: mass at t + 2
+    MassTile* __restrict__ partial1;      // per workgroup: mass at t + 1
+    MassTile* __restrict__ partial2;      // per workgroup: mass at t + 2
     const int* __restrict__ lmeta;        // link tables (see BndArgs)
     const double* __restrict__ lc;
     const double* __restrict__ luw;
@@ -378,11 +378,12 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
         step(k + 2, C, A);
     }
 
-    const MassPart v1 = mass_wave_part(msum1.a, msum1.b, a.mass.inv);
-    const MassPart v2 = mass_wave_part(msum2.a, msum2.b, a.mass.inv);
+    const double inv = mass_unit_inv(a.mass.magic), unit = mass_unit(a.mass.magic);
+    const MassPart v1 = mass_wave_part(msum1.a, msum1.b, inv);
+    const MassPart v2 = mass_wave_part(msum2.a, msum2.b, inv);
     if (j == 0) {
-        a.partial1[tile] = v1;
-        a.partial2[tile] = v2;
+        a.partial1[tile] = mass_pack(v1, unit);
+        a.partial2[tile] = mass_pack(v2, unit);
     }
 }
 

@@ -57,10 +57,22 @@ __host__ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 // once, at the end, and has the same bits for every tile shape, for one or
 // several steps per launch, alone or in a batch.  In a run that breaks down
 // the sums round as FP64 sums do, and become non-finite with the densities.
+// The unit, a power of two, goes about as 1.5 * 2^52 units: (x + magic) - magic
+// is x in whole units.  The unit and its inverse come from its exponent where a
+// tile ends; as arguments of their own they stayed in scalar registers over the
+// rows, of which the FP16 per-node form has too few (8192 x 4096: 389 us a launch
+// with them, 385 without).
 struct MassUnit {
-    double magic;  // 1.5 * 2^52 units: (x + magic) - magic is x in whole units
-    double unit, inv;  // inv = 1 / unit, both powers of two
+    double magic;
 };
+__host__ __device__ __forceinline__ double mass_unit(double magic) {
+    const long long e = (__builtin_bit_cast(long long, magic) >> 52) - 52;
+    return __builtin_bit_cast(double, e << 52);
+}
+__host__ __device__ __forceinline__ double mass_unit_inv(double magic) {
+    const long long e = (__builtin_bit_cast(long long, magic) >> 52) - 52;
+    return __builtin_bit_cast(double, (2046 - e) << 52);
+}
 constexpr double kMassFine = 1.0 / 1099511627776.0;
 struct MassPart {
     long long lo, hi;  // units: lo + 2^32 hi
@@ -169,6 +181,29 @@ __device__ __forceinline__ double mass_value(MassPart p, double unit) {
     const double s = h + l, e = l - (s - h);  // h + l = s + e
     return (s + fma(f, kMassFine, e)) * unit + p.big;
 }
+// A workgroup's part in memory.  One workgroup of the next launch reads them
+// all, so their bytes and the loads it has in flight count: at 8192 x 4096 the
+// boundary launch that sums two steps of 16-row tiles takes 29 us with these 16
+// bytes a tile and 16 loads a lane, 41 with 8 loads, and 51 with the 32 bytes of
+// a MassPart and 4 loads (one step of 9-row tiles: 13.0, 15.5, 18.8).
+struct alignas(16) MassTile {
+    long long units;  // or, with fine < 0, the bits of an FP64 mass: a part that
+    long long fine;   // integers do not hold.  fine: of 2^-40 units
+};
+// (a workgroup's units fit 63 bits: at most 1024 lanes of 2^53 each)
+__device__ __forceinline__ MassTile mass_pack(MassPart v, double unit) {
+    mass_carry(v);
+    const long long n = v.hi * 4294967296ll + v.lo;
+    if (v.big == 0.0) return MassTile{n, v.fine};
+    return MassTile{__builtin_bit_cast(long long, double(n) * unit + v.big), -1ll};
+}
+__device__ __forceinline__ void mass_take(MassPart& v, const MassTile& p) {
+    const bool in = p.fine >= 0;
+    v.lo += in ? p.units & 0xffffffffll : 0ll;
+    v.hi += in ? p.units >> 32 : 0ll;
+    v.fine += in ? p.fine : 0ll;
+    v.big += in ? 0.0 : __builtin_bit_cast(double, p.units);
+}
 
 template <typename S>
 struct MainArgs {
@@ -179,7 +214,7 @@ struct MainArgs {
     const float* __restrict__ psiw;     // FP16 storage: psi_w of solid nodes
     double* __restrict__ side_mom;      // [slot][3]: rho, ux, uy
     double* __restrict__ side_f;        // [slot][9]: pre-collision f
-    MassPart* __restrict__ partial;     // per workgroup
+    MassTile* __restrict__ partial;     // per workgroup
     double* mom_out[3];                 // moments mode: rho, ux, uy (null: not wanted)
     int nx, ny, pitch;
     long long plane;                    // elements per population plane
@@ -579,13 +614,13 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
     }
 
     if constexpr (!MOMENTS) {
-        const MassPart v = mass_wave_part(msum.a, msum.b, a.mass.inv);
+        const MassPart v = mass_wave_part(msum.a, msum.b, mass_unit_inv(a.mass.magic));
         if ((tid & 63) == 0) wsum[tid >> 6] = v;
         __syncthreads();
         if (tid == 0) {
             MassPart t = wsum[0];
             for (int w = 1; w < (W + 63) / 64; ++w) mass_take(t, wsum[w]);
-            a.partial[tile] = t;
+            a.partial[tile] = mass_pack(t, mass_unit(a.mass.magic));
         }
     }
 }
@@ -595,20 +630,23 @@ __global__ __launch_bounds__(256) void k_main(MainArgs<S> a, Phys<R> ph) {
     main_tile<S, R, EOS, MOMENTS, DEV, SAVEF>(a, ph, xcd_tile(blockIdx.x, gridDim.x));
 }
 
-// The partials lane `lane` of `lanes` adds up.
-__device__ __forceinline__ MassPart sum_partials(const MassPart* __restrict__ partial, int np,
+// The partials lane `lane` of `lanes` adds up.  (DEPTH is 16, but 8 in k_block,
+// whose registers are counted: with 16, FP32 arithmetic spills 45 of them and
+// 8192 x 4096 takes 451 us a step instead of 418.)
+template <int DEPTH>
+__device__ __forceinline__ MassPart sum_partials(const MassTile* __restrict__ partial, int np,
                                                  int lane, int lanes) {
     MassPart v{0, 0, 0, 0.0};
-    // four loads are issued before their additions
-    int i = lane;
-    for (; i + 3 * lanes < np; i += 4 * lanes) {
-        MassPart q[4];
+    // DEPTH loads are issued before their additions (past the end they give 0)
+    const rsrc_t rp = make_rsrc(partial, (unsigned)np * (unsigned)sizeof(MassTile));
+    for (int i = lane; i < np; i += DEPTH * lanes) {
+        uint4_t q[DEPTH];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) q[j] = partial[i + j * lanes];
+        for (int j = 0; j < DEPTH; ++j)
+            q[j] = bload<uint4_t>(rp, (unsigned)(i + j * lanes) * (unsigned)sizeof(MassTile), 0u);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) mass_take(v, q[j]);
+        for (int j = 0; j < DEPTH; ++j) mass_take(v, __builtin_bit_cast(MassTile, q[j]));
     }
-    for (; i < np; i += lanes) mass_take(v, partial[i]);
     mass_carry(v);
     return v;
 }
@@ -618,17 +656,18 @@ constexpr int kReduceWaves = 16;  // of a workgroup that sums partials, at most
 // The masses of `steps` steps, whose np partials each lie `stride` apart, by
 // one workgroup: the wavefronts share the steps (all of them one step if
 // there is only one), and put(s, mass) runs in thread 0, in step order.
-template <typename F>
-__device__ __forceinline__ void sum_masses(const MassPart* __restrict__ partial, int np, int steps,
+template <int DEPTH, typename F>
+__device__ __forceinline__ void sum_masses(const MassTile* __restrict__ partial, int np, int steps,
                                            long long stride, double unit, F&& put) {
     __shared__ MassPart red[kReduceWaves];
-    const int nw = (int)blockDim.x / 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nw = (int)blockDim.x / 64, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     for (int s0 = 0; s0 < steps; s0 += nw) {
         const int cnt = min(nw, steps - s0), share = nw / cnt;  // wavefronts of a step
         const int s = wave / share, part = wave - s * share;
         if (s < cnt) {
-            const MassPart v = mass_wave_sum(sum_partials(partial + (s0 + s) * stride, np,
-                                                          part * 64 + lane, share * 64));
+            const MassPart v = mass_wave_sum(sum_partials<DEPTH>(partial + (s0 + s) * stride, np,
+                                                                 part * 64 + lane, share * 64));
             if (lane == 0) red[wave] = v;
         }
         __syncthreads();
@@ -648,7 +687,7 @@ __device__ __forceinline__ void sum_masses(const MassPart* __restrict__ partial,
 // step then need no argument that changes from step to step, so a captured
 // graph of steps can be replayed.
 struct MassPass {
-    const MassPart* __restrict__ partial;
+    const MassTile* __restrict__ partial;
     int np, steps;
     long long stride;
     double unit;
@@ -657,9 +696,10 @@ struct MassPass {
     long long* __restrict__ clock;   // step of the last recorded mass
     long long* __restrict__ unstable;
 };
+template <int DEPTH>
 __device__ __forceinline__ void reduce_pass(const MassPass& r) {
     long long t = threadIdx.x == 0 ? *r.clock : 0;
-    sum_masses(r.partial, r.np, r.steps, r.stride, r.unit, [&](int, double m) {
+    sum_masses<DEPTH>(r.partial, r.np, r.steps, r.stride, r.unit, [&](int, double m) {
         ++t;
         r.hist[t % r.cap] = m;
         if (!isfinite(m) && *r.unstable < 0) *r.unstable = t;
@@ -669,7 +709,7 @@ __device__ __forceinline__ void reduce_pass(const MassPass& r) {
 
 template <int Unused = 0>
 __global__ __launch_bounds__(256) void k_reduce(MassPass r) {
-    reduce_pass(r);
+    reduce_pass<16>(r);
 }
 
 // ---------------------------------------------------------------- boundary
@@ -974,7 +1014,7 @@ __device__ __forceinline__ void open_rows(S* __restrict__ A, const BndArgs& b, i
 template <typename S, int DEV>
 __global__ __launch_bounds__(256) void k_boundary(S* __restrict__ A, BndArgs b) {
     if (blockIdx.x == gridDim.x - 1) {
-        if (b.do_reduce) reduce_pass(b.prev);
+        if (b.do_reduce) reduce_pass<16>(b.prev);
         return;
     }
     if (int(blockIdx.x) >= b.nlink_blocks) {
@@ -1047,7 +1087,7 @@ struct BInst {
     const float* psiw;
     double* side_mom[2];  // of the times of f[0], f[1] (or one for both)
     double* side_f;
-    MassPart* partial;  // one mass partial per tile
+    MassTile* partial;  // one mass partial per tile
     MassUnit mass;
     int nx, ny, pitch, nsegs, nstrips, np;
     unsigned side_mom_bytes, side_f_bytes;
@@ -1104,8 +1144,6 @@ __device__ __forceinline__ MainArgs<S> inst_main_args(const I_t& I, int c, int t
     a.side_f = I.side_f;
     a.partial = I.partial;
     a.mass.magic = I.mass.magic;
-    a.mass.unit = I.mass.unit;
-    a.mass.inv = I.mass.inv;
     for (double*& p : a.mom_out) p = nullptr;
     a.nx = I.nx;
     a.ny = I.ny;
@@ -1220,7 +1258,7 @@ __global__ __launch_bounds__(256) void k_reduce_batch(BatchArgs b) {
         const auto& I = ro(b.inst)[i];
         const long long t1 = st->t + 1;
         __syncthreads();
-        sum_masses(I.partial, I.np, 1, 0, I.mass.unit, [&](int, double m) {
+        sum_masses<16>(I.partial, I.np, 1, 0, mass_unit(I.mass.magic), [&](int, double m) {
             I.hist[t1 % I.cap] = m;
             if (!isfinite(m) && *I.unstable < 0) *I.unstable = t1;
         });

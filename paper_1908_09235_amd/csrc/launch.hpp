@@ -23,7 +23,7 @@ struct Ctx {
     double* side_f;
     unsigned side_mom_bytes, side_f_bytes;
     bool save_f;  // boundary nodes save pre-collision populations (Zhao-Yong)
-    MassPart* partial;
+    MassTile* partial;
     MassUnit mass;
     double* mom_out[3];  // moments mode: rho, ux, uy planes (null: not wanted)
     const float* ref;  // init: density plane of the buffer being filled (or null)
@@ -33,7 +33,7 @@ struct Ctx {
     int tile_h2, nsegs2, nstrips2, nblocks2;
     const int* node_link;
     const int* tile_order;  // two-step pass: tile of each workgroup
-    MassPart* partial2;
+    MassTile* partial2;
     const int* lmeta;
     const double* lc;
     const double* luw;

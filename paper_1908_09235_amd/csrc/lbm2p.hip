@@ -333,7 +333,7 @@ MassPass mass_pass(lbm_domain* d) {
         r.np = d->pending_steps == 2 ? d->nblocks2 : d->nblocks;
         r.stride = d->partial_cap;
     }
-    r.unit = d->mass.unit;
+    r.unit = mass_unit(d->mass.magic);
     r.hist = d->hist;
     r.cap = d->cap;
     r.clock = d->clock;
@@ -868,7 +868,7 @@ int place_blocks(lbm_domain* d, const BlockTables& b) {
     const size_t tiles = b.tiles.size() * sizeof(BlockTile);
     const size_t links = b.links.size() * sizeof(BlockLink);
     const size_t nodes = b.nodes.size() * sizeof(BlockNode);
-    const size_t part = (size_t)b.steps * b.tiles.size() * sizeof(MassPart);
+    const size_t part = (size_t)b.steps * b.tiles.size() * sizeof(MassTile);
     const size_t mom = (size_t)3 * std::max(d->nslots, 1) * 8;
     // one piece of memory; a domain that leaves no room for it takes single steps
     char* m = nullptr;
@@ -901,7 +901,7 @@ int place_blocks(lbm_domain* d, const BlockTables& b) {
 }
 
 // The unit of the mass sums (see MassUnit) from the largest initial density.
-MassUnit mass_unit(const lbm_desc* s, long long n) {
+MassUnit mass_unit_for(const lbm_desc* s, long long n) {
     double mx = 0.0;
     for (long long i = 0; i < n; ++i)
         if (!s->solid[i] && s->rho0[i] > mx) mx = s->rho0[i];
@@ -911,7 +911,7 @@ MassUnit mass_unit(const lbm_desc* s, long long n) {
     int e = 0;
     (void)std::frexp(mx, &e);  // mx < 2^e
     const double unit = std::ldexp(1.0, e - 40);
-    return MassUnit{1.5 * std::ldexp(unit, 52), unit, 1.0 / unit};
+    return MassUnit{1.5 * std::ldexp(unit, 52)};
 }
 
 int validate_and_build(const lbm_desc* s, lbm_domain* d) {
@@ -1037,7 +1037,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
         for (long long i = 0; i < N; i += nx)
             if (!cs_psi_finite(s->rho0 + i, s->solid + i, nx, d->ph64)) return LBM_EINVAL;
     d->fluid = fluid;
-    d->mass = mass_unit(s, N);
+    d->mass = mass_unit_for(s, N);
     if (s->storage == LBM_STORE_F32DEV || s->storage == LBM_STORE_F16DEV) {
         double rref = s->rho_ref;
         if (rref == 0.0 && fluid > 0) {
@@ -1279,7 +1279,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     if (d->fusable)  // and for two-step tiles down to kMinTileH2 rows
         d->partial_cap = std::max(d->partial_cap,
                                   d->nstrips2 * ((ny + kMinTileH2 - 1) / kMinTileH2));
-    const size_t pbytes = (size_t)(d->fusable ? 2 : 1) * d->partial_cap * sizeof(MassPart);
+    const size_t pbytes = (size_t)(d->fusable ? 2 : 1) * d->partial_cap * sizeof(MassTile);
     if (d->arena) {
         // In an arena (batched and served instances) the read-out buffer is
         // part of the footprint, so that reading a finished instance never
@@ -1287,7 +1287,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
         // fields can be read.
         if ((rc = dev_alloc(d, (void**)&d->mom_out, std::max<size_t>((size_t)3 * N * 8, pbytes))))
             return rc;
-        d->partial = reinterpret_cast<MassPart*>(d->mom_out);
+        d->partial = reinterpret_cast<MassTile*>(d->mom_out);
     } else if ((rc = dev_alloc(d, (void**)&d->partial, pbytes))) {
         return rc;
     }
@@ -1441,7 +1441,7 @@ bool domain_make_blocks(lbm_domain* d, int steps, Arena* pool) {
     p.tiles = static_cast<BlockTile*>(pool->alloc(nt * sizeof(BlockTile)));
     p.links = static_cast<BlockLink*>(pool->alloc(b.links.size() * sizeof(BlockLink)));
     p.nodes = static_cast<BlockNode*>(pool->alloc(b.nodes.size() * sizeof(BlockNode)));
-    p.partial[0] = static_cast<MassPart*>(pool->alloc((size_t)steps * nt * sizeof(MassPart)));
+    p.partial[0] = static_cast<MassTile*>(pool->alloc((size_t)steps * nt * sizeof(MassTile)));
     bool ok = p.tiles && p.links && p.nodes && p.partial[0];
     auto put = [&](void* dst, const void* src, size_t n) {
         if (ok && n)

@@ -100,3 +100,20 @@ def test_densities_of_any_size(L, rho):
             want = _sum(d.moments()[0])
             say(f"    t = {d.t}: {d.total_mass()!r}, {float(want)!r}")
             assert _close(d.total_mass(), want)
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 64), (1300, 1250)])
+@pytest.mark.parametrize("form", ["single steps", "blocks"])
+def test_densities_beyond_the_units(L, form, nx, ny):
+    # too large for the integers: the parts are FP64 sums, whose error is at
+    # most a rounding a term
+    p = _still(nx, ny, np.full((ny, nx), 1.7e280))
+    say(f"[gpu] mass of {nx}x{ny} densities of 1.7e280, {form}")
+    with L.Domain(p, storage="f64", history_capacity=64) as d:
+        if form == "single steps":
+            L.lbm_set_profiling(d.h, 1)
+        d.step(9)
+        want = _sum(d.moments()[0])
+        hist = d.mass_history()
+        say(f"    {hist[-1]!r}, {float(want)!r}")
+        assert np.all(np.abs(hist - float(want)) <= nx * ny * 2.0 ** -53 * float(want))
