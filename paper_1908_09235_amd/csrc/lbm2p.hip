@@ -187,8 +187,13 @@ inline int wrapi(int i, int n) { return ((i % n) + n) % n; }
 // 25.2 and 29.3); 1500 x 1400 77.8 / 73.0 / 72.4 and 71.2.
 constexpr long long kSmallNodes = 500000;   // 3 rows
 constexpr long long kMediumNodes = 1200000; // 6 rows
-int default_tile_h(int nx, int ny) {
+// The FP16 per-node form, whose halo rows cost most, takes 15 rows of large
+// lattices: 3999 x 2001 9 rows 112.0, 15 rows 111.9; 4096^2 215.2 and 212.1; 6000 x
+// 3000 225.2 and 216.7; 8192 x 4096 398.5 and 387.0 (256 columns).
+constexpr long long kLargeNodes = 12000000;
+int default_tile_h(int nx, int ny, int storage) {
     const long long n = (long long)nx * ny;
+    if (storage == LBM_STORE_F16NODE && n > kLargeNodes) return 15;
     return n <= kSmallNodes ? 3 : n <= kMediumNodes ? 6 : 9;
 }
 
@@ -198,15 +203,21 @@ int default_tile_h(int nx, int ny) {
 // faster at equal share); within 2 % for the FP16 per-node form, whose rings
 // of densities make idle lanes dearer (2048^2: 68.9 us a step with 256 columns
 // and a share of 0.89, 62.2 with 128 and 0.94; 3999 x 2001, 0.98 either way:
-// 109.1 and 111.4).
+// 109.1 and 111.4).  Its tiles of 64 columns hold as much LDS as the wider ones,
+// for a quarter of the wavefronts, so beyond small lattices a share of theirs
+// counts less (64, 128 and 256 columns: 1200 x 1000 by 6 rows 35.3, 30.5 and 31.9;
+// 1408^2 by 9 rows 45.3, 38.8 and 39.6 with shares of 0.96, 0.92 and 0.92; 2048^2
+// 71.9, 64.2 and 70.2).
 int default_tile_w(int nx, int ny, int storage) {
-    if ((long long)nx * ny <= kMediumNodes) return 64;
+    const bool node = storage == LBM_STORE_F16NODE;
+    if ((long long)nx * ny <= (node ? kSmallNodes : kMediumNodes)) return 64;
     double eff[3], best = 0.0;
     const int ws[3] = {256, 128, 64};
-    const double near = storage == LBM_STORE_F16NODE ? 0.98 : 0.9;
+    const double near = node ? 0.98 : 0.9;
     for (int k = 0; k < 3; ++k) {
         const int ns = (nx + strip_cols(ws[k]) - 1) / strip_cols(ws[k]);
         eff[k] = (double)nx / ((double)ns * ws[k]);
+        if (node && ws[k] == 64) eff[k] *= 0.88;
         best = std::max(best, eff[k]);
     }
     for (int k = 0; k < 3; ++k)
@@ -1066,7 +1077,7 @@ int validate_and_build(const lbm_desc* s, lbm_domain* d) {
     d->open_x = s->open_x;
     d->inlet_u = s->open_x ? s->inlet_u : 0.0;
     d->tile_w = s->tile_w ? s->tile_w : default_tile_w(nx, ny, d->storage);
-    d->tile_h = s->tile_h ? s->tile_h : default_tile_h(nx, ny);
+    d->tile_h = s->tile_h ? s->tile_h : default_tile_h(nx, ny, d->storage);
     d->nstrips = (nx + strip_cols(d->tile_w) - 1) / strip_cols(d->tile_w);
     d->nsegs = seg_count(ny, d->tile_h);
     d->nblocks = d->nstrips * d->nsegs;

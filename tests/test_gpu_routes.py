@@ -127,6 +127,17 @@ def test_a_refused_setting_changes_nothing(L):
                 assert d.blocks() == on, (steps, refused)
 
 
+def test_default_tiles_of_the_per_node_form(L):
+    """64 columns only where a lattice is small or narrow: a tile's LDS does not
+    shrink with its columns."""
+    for nx, ny, want in ((300, 300, (64, 3)), (1200, 1000, (256, 6)), (1408, 1408, (256, 9)),
+                         (2048, 2048, (128, 9)), (50, 20000, (64, 6)), (4064, 3000, (256, 15))):
+        with L.Domain(_free(nx, ny), storage="f16node", history_capacity=16) as d:
+            i = d.info()
+            say(f"[gpu] {nx}x{ny}: tiles of {i['tile_w']}x{i['tile_h']}")
+            assert (i["tile_w"], i["tile_h"]) == want
+
+
 def test_tables_that_do_not_fit_a_block(L):
     """With a third of the nodes solid a block of 32 x 32 has more links than a
     workgroup has lanes."""
