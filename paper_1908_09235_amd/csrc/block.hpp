@@ -437,9 +437,9 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         // ---- force, moments, collision
         const bool last = s == steps;
         constexpr bool SPLIT = sizeof(R) == 8 || DEV != 0;
-        MassSum<SPLIT> msum;
         MassUnit mass;
         mass.magic = a.mass.magic;
+        MassSum<SPLIT> msum(mass);
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
             const int n = t + j * NT;
@@ -456,7 +456,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
                 R rho, drho, ux, uy, Fx, Fy;
                 node_moments<R, EOS, DEV>(fc, ps, ph, rho, drho, ux, uy, Fx, Fy);
                 const double rho_d = DEV == 1 ? double(ph.rref) + double(drho) : double(rho);
-                msum.add(own, rho_d, mass);
+                msum.add(own, rho_d);
                 const int rec = (int)(fact(j) >> 6 & 0x3ffu) - 1;
                 if (rec >= 0) {
                     mom[3 * rec] = rho_d;
@@ -480,10 +480,10 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         // into the step's bins, as integers (FP64 atomics in LDS took the
         // droplet at 2048^2 in FP64 from 107 to 120 us a step)
         {
-            const double x = msum.a + mass.magic;
-            const double y = msum.b + (SPLIT ? 0.0 : msum.a - (x - mass.magic));
+            const double x = SPLIT ? msum.a : msum.a + mass.magic, u = x - mass.magic;
+            const double y = SPLIT ? msum.b : msum.a - u;
             const double z = y + mass.magic * kMassFine;
-            const bool in = fabs(msum.a) < 0.25 * mass.magic;  // 1.5 * 2^50 units
+            const bool in = fabs(u) < 0.25 * mass.magic;  // 1.5 * 2^50 units
             const long long q = __builtin_bit_cast(long long, x) -
                                 __builtin_bit_cast(long long, mass.magic);
             const long long fn = __builtin_bit_cast(long long, z) -
@@ -493,7 +493,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
                 atomicAdd(&mfine[s - 1][t % kBlockBins], (unsigned long long)fn);
             }
             if (__builtin_amdgcn_ballot_w64(!in)) {  // not in a stable run
-                double v = in ? 0.0 : msum.a + msum.b;
+                double v = in ? 0.0 : u + y;
                 for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
                 if (lane == 0) mbig[s - 1][wave] = v;
             }

@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
         ps[8] = ring[km][cr];
     };
 
-    MassSum<sizeof(R) == 8 || DEV != 0> msum1, msum2;
+    MassSum<sizeof(R) == 8 || DEV != 0> msum1(a.mass), msum2(a.mass);
     Pull2<S> fcur{}, fnxt{};      // pulled f(t + 2) of rows k - 2 and k - 1
 
     // the wall rules of step t + 2 for the boundary node of lane j in row m
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
             R rho, drho, ux, uy, Fx, Fy;
             node_moments<R, EOS, DEV>(fc, ps, ph, rho, drho, ux, uy, Fx, Fy);
             const double rho_d = DEV == 1 ? double(ph.rref) + double(drho) : double(rho);
-            msum1.add(fluid && outc && k >= 3 && k < H + 3, rho_d, a.mass);
+            msum1.add(fluid && outc && k >= 3 && k < H + 3, rho_d);
             R dh[9];
             collide<R>(fc, rho, drho, ux, uy, Fx, Fy, ph, dh);
             const int s = r1(k);
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
             R rho, drho, ux, uy, Fx, Fy;
             node_moments<R, EOS, DEV>(fc, ps, ph, rho, drho, ux, uy, Fx, Fy);
             const double rho_d = DEV == 1 ? double(ph.rref) + double(drho) : double(rho);
-            msum2.add(live, rho_d, a.mass);
+            msum2.add(live, rho_d);
             const bool sm = live && (nf & FL_SAVE_MOM);
             if (__builtin_amdgcn_ballot_w64(sm)) {
                 const unsigned so = sm ? (unsigned)msi[rm(n)][j] * 24u : kOOB;
@@ -379,8 +379,8 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
     }
 
     const double inv = mass_unit_inv(a.mass.magic), unit = mass_unit(a.mass.magic);
-    const MassPart v1 = mass_wave_part(msum1.a, msum1.b, inv);
-    const MassPart v2 = mass_wave_part(msum2.a, msum2.b, inv);
+    const MassPart v1 = mass_wave_part(msum1.sum(a.mass), msum1.b, inv);
+    const MassPart v2 = mass_wave_part(msum2.sum(a.mass), msum2.b, inv);
     if (j == 0) {
         a.partial1[tile] = mass_pack(v1, unit);
         a.partial2[tile] = mass_pack(v2, unit);

@@ -49,14 +49,15 @@ __host__ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 }
 
 // Total mass.  The FP64 density of every fluid node is split, exactly, into a
-// multiple of `unit` (2^-40 of the largest initial density, or a little more)
-// and the rest, and both are added in FP64.  Sums of such multiples below
-// 2^53 units are exact (128 times the initial density and more, at every
-// place here), and so are those of the rests, whatever the order; the sums of
-// lanes, tiles and workgroups go on as integers.  So a step's mass is rounded
-// once, at the end, and has the same bits for every tile shape, for one or
-// several steps per launch, alone or in a batch.  In a run that breaks down
-// the sums round as FP64 sums do, and become non-finite with the densities.
+// multiple of a unit (2^-40 of the largest initial density, or a little more)
+// and the rest, and both are added in FP64.  The sums of lanes, tiles and
+// workgroups go on as integers, so a step's mass is rounded once, at the end, and
+// has the same bits for every tile shape, for one or several steps per launch,
+// alone or in a batch.  That holds while a lane's multiples stay below 2^53 units:
+// densities up to 2^13 / rows times the largest initial one (910 times in the
+// default tiles, 4 times in the tallest; 768 times in k_block); and while rests
+// are whole 2^-40ths of a unit, down to 2^-28 of it.  Beyond, in a run that breaks
+// down, the sums round as FP64 sums do, and become non-finite with the densities.
 // The unit, a power of two, goes about as 1.5 * 2^52 units: (x + magic) - magic
 // is x in whole units.  The unit and its inverse come from its exponent where a
 // tile ends; as arguments of their own they stayed in scalar registers over the
@@ -89,8 +90,8 @@ __device__ __forceinline__ void mass_carry(MassPart& v) {
     v.hi += v.lo >> 32;
     v.lo &= 0xffffffffll;
 }
-// Rows one lane adds up at most: 2^51 units each, in 63 bits.  A tile of more
-// rows runs as several.
+// Rows one lane adds up at most: 2^51 units of the largest initial density.  A
+// tile of more rows runs as several.
 constexpr int kMassRows = 2048;
 __host__ __device__ constexpr int seg_rows(int tile_h) {
     return tile_h < kMassRows ? tile_h : kMassRows;
@@ -99,20 +100,31 @@ __host__ __device__ constexpr int seg_count(int ny, int tile_h) {
     return (ny + seg_rows(tile_h) - 1) / seg_rows(tile_h);
 }
 
-// What one lane adds up.  SPLIT: as above.  An FP32 density is a multiple of
-// the unit as it is (down to 2^-16 of the largest).
+// What one lane adds up.  SPLIT: as above.  The sum starts at 1.5 * 2^52 units, so
+// that adding a density leaves whole units in it, and what the addition rounded
+// off is the rest (the sum is the larger of the two, so the difference is exact).
+// An FP32 density is a multiple of the unit as it is (down to 2^-16 of the
+// largest).  Splitting the density before adding it took an operation more and
+// two registers: 3000 x 2000 FP16 per-node 86.3 us a step and 85.1 so, the two-step
+// kernel at 2048^2 in FP32 157.5 us a launch and 155.9, FP16 deviations 8192 x 4096
+// 627 and 619.
 template <bool SPLIT>
 struct MassSum {
-    double a = 0.0, b = 0.0;
-    __device__ __forceinline__ void add(bool live, double rho, const MassUnit& m) {
+    double a, b;
+    __device__ __forceinline__ explicit MassSum(const MassUnit& m)
+        : a(SPLIT ? m.magic : 0.0), b(0.0) {}
+    __device__ __forceinline__ void add(bool live, double rho) {
         const double r = live ? rho : 0.0;
         if constexpr (SPLIT) {
-            const double x = (r + m.magic) - m.magic;
-            a += x;
-            b += r - x;
+            const double s = a + r;
+            b += r - (s - a);
+            a = s;
         } else {
             a += r;
         }
+    }
+    __device__ __forceinline__ double sum(const MassUnit& m) const {
+        return SPLIT ? a - m.magic : a;
     }
 };
 
@@ -161,8 +173,8 @@ __device__ __forceinline__ MassPart mass_wave_sum(const MassPart& p) {
 // lane 0 (at most 2^53 units a lane: 64 of them fit an integer as they are).
 __device__ __forceinline__ MassPart mass_wave_part(double a, double b, double inv) {
     const double n = a * inv, r = b * inv;
-    // (the rests of kMassRows nodes, half a unit each: 64 lanes of them hold)
-    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= 0.5 * kMassRows;
+    // (the rests of kMassRows nodes, a unit each at most: 64 lanes of them hold)
+    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= kMassRows;
     // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
     const double w = rint(n);
     const long long q = wave_total(in ? (long long)w : 0ll);
@@ -504,7 +516,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
         ring[slot][tid] = (L.fl & FL_SOLID) ? pw : psi_of<EOS, R>(rho, ph);
     };
 
-    MassSum<sizeof(R) == 8 || DEV != 0> msum;
+    MassSum<sizeof(R) == 8 || DEV != 0> msum(a.mass);
     // row k: collide with psi of rows k-1, k, k+1; then prefetch row k+3
     auto step = [&](int k, RowLoad<S, R, NR>& Lc, RowLoad<S, R, NR>& Ln) {
         const int y = row_of(k);
@@ -543,7 +555,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
 #pragma unroll
                 for (int q = 0; q < 9; ++q) rho_d += fma(wt(q), double(rr[q]), double(Lc.f[q]));
             }
-            msum.add(live, rho_d, a.mass);
+            msum.add(live, rho_d);
             // moments of boundary nodes (and pre-collision populations)
             // (stores only from a wavefront with such a node in the row:
             // the branch is uniform, and the waits for the rows in flight
@@ -614,7 +626,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
     }
 
     if constexpr (!MOMENTS) {
-        const MassPart v = mass_wave_part(msum.a, msum.b, mass_unit_inv(a.mass.magic));
+        const MassPart v = mass_wave_part(msum.sum(a.mass), msum.b, mass_unit_inv(a.mass.magic));
         if ((tid & 63) == 0) wsum[tid >> 6] = v;
         __syncthreads();
         if (tid == 0) {
