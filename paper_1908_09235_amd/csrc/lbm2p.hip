@@ -464,14 +464,27 @@ void launch_pass(lbm_domain* d, bool two, hipEvent_t* rec) {
 
 // Runs of steps go through k_block where the domain has a plan for it, also
 // with two steps per pass asked for, but for rows per tile asked for with them,
-// which name the two-step kernel, and large domains without walls, where its
-// tiles have no wall rules to wait for (free droplet, FP32, us a step in blocks
-// and in the two-step kernel: 1024^2 14.8 and 22.1, 2048^2 55.8 and 50.0, 2304 x
-// 2048 64.4 and 56.2; with walls 2048^2 52 and 85).
+// which name the two-step kernel, and for large two-phase domains, of which a
+// step in blocks works the halos twice over (a single phase needs half of them).
+// us a step in blocks and in the two-step kernel by its default rows, FP32
+// arithmetic (FP32 deviations):
+//   without walls   1024^2 14.8 and 22.1, 2048^2 58.6 and 49.1, 8192 x 4096 412
+//     and 330: the two-step kernel from three million nodes on;
+//   with walls its launch waits for the tiles that hold most of them, until
+//   there are enough others, and each link costs it four times as much: 24
+//     to 60 cylinders, 4096 x 2048 110 and 126 (114, 126), 4096 x 3000 154 and 155
+//     (163, 155), 4096 x 3500 180 and 171 (191, 171), 8192 x 4096 414 and 386 (435,
+//     386); 4096^2 with links to 0.3 % of the nodes 207 and 195, 1.1 % 220 and 254,
+//     1.6 % 227 and 282;
+//   single phase    2048^2 37.2 and 45.4, 8192 x 4096 268 and 322, 4096^2 with
+//     pillars 171 and 409: blocks.
 bool uses_blocks(const lbm_domain* d) {
     if (d->block.steps == 0) return false;
     if (d->fused != 2) return true;
-    return !d->tile_h2_asked && !(d->nl == 0 && d->fluid > 3000000);
+    if (d->tile_h2_asked) return false;
+    if (d->eos == LBM_EOS_NONE) return true;
+    if (d->nl == 0) return d->fluid <= 3000000;
+    return d->fluid <= 13000000 || 200LL * d->nl >= d->fluid;
 }
 
 // k steps in one launch of k_block, which also records the masses of the

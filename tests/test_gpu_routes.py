@@ -127,6 +127,26 @@ def test_a_refused_setting_changes_nothing(L):
                 assert d.blocks() == on, (steps, refused)
 
 
+@pytest.mark.parametrize("eos,nx,ny,period,blocks", [
+    ("exp", 1700, 1700, 0, True), ("exp", 1800, 1700, 0, False),    # no walls
+    ("none", 1800, 1700, 0, True),                                  # single phase
+    ("exp", 3500, 3500, 64, True), ("exp", 3700, 3700, 64, False),  # few links
+    ("exp", 3700, 3700, 32, True), ("none", 3700, 3700, 64, True)])
+def test_blocks_or_the_two_step_kernel(L, eos, nx, ny, period, blocks):
+    p = _free(nx, ny, eos)
+    if period:
+        w = _pillars(nx, ny, period)
+        p = p.with_(solid=w.solid, links=w.links, rule="halfway", fix="none")
+    with L.Domain(p, storage="f32_arith32", history_capacity=16) as d:
+        assert d.blocks()[0] >= 2
+        L.lbm_set_steps_per_pass(d.h, 2)
+        say(f"[gpu] two steps per pass, {eos} {nx}x{ny}, {len(p.links)} links: {d.blocks()}")
+        assert (d.blocks()[0] >= 2) == blocks
+        before = d.total_mass()
+        d.step(4)
+        assert abs(d.total_mass() - before) <= 1e-6 * before
+
+
 def test_default_tiles_of_the_per_node_form(L):
     """64 columns only where a lattice is small or narrow: a tile's LDS does not
     shrink with its columns."""
