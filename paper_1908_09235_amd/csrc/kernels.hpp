@@ -1186,11 +1186,23 @@ __device__ __forceinline__ void batch_tile(const BatchArgs& b, int g) {
 // the other queues in turn, until all are empty.  The queues hold
 // contiguous runs of the tile list, so one XCD works through compact
 // pieces of the same instances and finds their halos in its L2.
+// Wavefronts per SIMD to keep: three at least (a ring of four rows would
+// otherwise take more registers than three leave), and those of the forms whose
+// registers end just above the limit of one more (FP16 per-node, 256 instances
+// of 57 M nodes: 756 us a step with 130 registers and three wavefronts, 701 with
+// four).
+template <typename S, typename R>
+constexpr int batch_waves(int eos, int dev, bool savef, int ring) {
+    if (dev == 2) return savef && eos != EOS_NONE ? 3 : 4;
+    if (savef) return 3;
+    if (sizeof(R) == 8) return sizeof(S) == 8 && eos == EOS_EXP && ring == 2 ? 4 : 3;
+    if (eos == EOS_NONE && ring == 2) return 6;
+    return eos == EOS_CS && ring == 4 && dev == 0 ? 4 : 3;
+}
 template <typename S, typename R, int EOS, int DEV, bool SAVEF, int RING>
-// (at least three wavefronts per SIMD: a ring of four rows would otherwise
-// take more registers than three leave)
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_main_batch(
-    BatchArgs b) {
+__global__ __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(batch_waves<S, R>(EOS, DEV, SAVEF, RING)))) void
+    k_main_batch(BatchArgs b) {
     if (!b.persistent) {
         batch_tile<S, R, EOS, DEV, SAVEF, RING>(b, xcd_tile(blockIdx.x, gridDim.x));
         return;
