@@ -281,7 +281,7 @@ int plan_batch(lbm_batch* b) {
                         b->ncu) + 4.7 / k;
     };
     for (int k = 2; k <= kBlockSteps; ++k)
-        if (tiles[k] > 0 && tiles[k] < (1 << 24) && cost(k) < best) {
+        if (tiles[k] > 0 && tiles[k] <= kBlockTiles && cost(k) < best) {
             best = cost(k);
             steps = k;
         }

@@ -50,6 +50,10 @@ constexpr int kBlockThreads = 512;
 // the side of the square region that a workgroup of `lanes` threads works on
 constexpr int kBlockSmall = 576;  // (24 x 24, one node a lane)
 constexpr int block_side(int lanes) { return lanes == kBlockSmall ? 24 : 32; }
+// tiles of a launch, at most: a launch has fewer than 2^32 lanes (and one
+// workgroup more than tiles)
+constexpr int kBlockTiles = (1 << 23) - 2;
+static_assert((kBlockTiles + 1ll) * kBlockThreads < 1ll << 32, "lanes of a launch");
 constexpr int kBlockNodes = kBlockThreads;  // moment records of a tile: one a thread
 // bytes of LDS for n moment records and their leaks
 constexpr unsigned block_lds(int n) { return 32u * (unsigned)n; }

@@ -740,7 +740,7 @@ bool block_tables(const lbm_domain* d, int steps, int lanes, const LinkTables& l
     if (own < 1) return false;
     b.nstrips = (d->nx + own - 1) / own;
     b.nsegs = (d->ny + own - 1) / own;
-    if ((long long)b.nstrips * b.nsegs >= (1 << 24)) return false;
+    if ((long long)b.nstrips * b.nsegs > kBlockTiles) return false;
     // the regions (and the place in them) that pull a column or row
     auto places = [&](int n, int parts, int width) {
         std::vector<std::vector<std::pair<int, int>>> v((size_t)n);
