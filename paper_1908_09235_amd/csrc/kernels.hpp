@@ -53,9 +53,10 @@ __host__ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 // and the rest, and both are added in FP64.  The sums of lanes, tiles and
 // workgroups go on as integers, so a step's mass is rounded once, at the end, and
 // has the same bits for every tile shape, for one or several steps per launch,
-// alone or in a batch.  That holds while a lane's multiples stay below 2^53 units:
-// densities up to 2^13 / rows times the largest initial one (910 times in the
-// default tiles, 4 times in the tallest; 768 times in k_block); and while rests
+// alone or in a batch.  That holds while the multiples that one lane adds up stay
+// below 2^53 units: densities up to 2^13 / (rows x wavefronts of a tile) times the
+// largest initial one (227 times in tiles of 9 rows by 256 columns, 4 times in
+// the tallest, 512 in the two-step kernel's and 768 in k_block); and while rests
 // are whole 2^-40ths of a unit, down to 2^-28 of it.  Beyond, in a run that breaks
 // down, the sums round as FP64 sums do, and become non-finite with the densities.
 // The unit, a power of two, goes about as 1.5 * 2^52 units: (x + magic) - magic
@@ -90,9 +91,9 @@ __device__ __forceinline__ void mass_carry(MassPart& v) {
     v.hi += v.lo >> 32;
     v.lo &= 0xffffffffll;
 }
-// Rows one lane adds up at most: 2^51 units of the largest initial density.  A
-// tile of more rows runs as several.
-constexpr int kMassRows = 2048;
+// Rows of a tile at most: 2^51 units of the largest initial density, with those of
+// the other wavefronts.  A tile of more rows runs as several.
+constexpr int kMassRows = 512;
 __host__ __device__ constexpr int seg_rows(int tile_h) {
     return tile_h < kMassRows ? tile_h : kMassRows;
 }
@@ -173,8 +174,8 @@ __device__ __forceinline__ MassPart mass_wave_sum(const MassPart& p) {
 // lane 0 (at most 2^53 units a lane: 64 of them fit an integer as they are).
 __device__ __forceinline__ MassPart mass_wave_part(double a, double b, double inv) {
     const double n = a * inv, r = b * inv;
-    // (the rests of kMassRows nodes, a unit each at most: 64 lanes of them hold)
-    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= kMassRows;
+    // (the rests of 4 kMassRows nodes, a unit each at most: 64 lanes of them hold)
+    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= 4 * kMassRows;
     // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
     const double w = rint(n);
     const long long q = wave_total(in ? (long long)w : 0ll);
@@ -365,8 +366,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
     // RING rows of loads: RING - 1 rows are in flight while a row is
     // computed (the FP16 per-node form's density ring assumes three)
     static_assert(RING >= 2 && RING <= 4 && (DEV != 2 || RING == 3), "unsupported ring");
-    __shared__ R ring[4][kMaxTileW];
-    __shared__ MassPart wsum[kMaxTileW / 64];
+    __shared__ alignas(16) R ring[4][kMaxTileW];
     constexpr unsigned ES = sizeof(S);
     // DEV 2: the density plane's rows -2 .. H + 1 of the strip, with one
     // column more on either side, pass through an LDS ring of eight rows:
@@ -626,13 +626,28 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
     }
 
     if constexpr (!MOMENTS) {
-        const MassPart v = mass_wave_part(msum.sum(a.mass), msum.b, mass_unit_inv(a.mass.magic));
-        if ((tid & 63) == 0) wsum[tid >> 6] = v;
-        __syncthreads();
-        if (tid == 0) {
-            MassPart t = wsum[0];
-            for (int w = 1; w < (W + 63) / 64; ++w) mass_take(t, wsum[w]);
-            a.partial[tile] = mass_pack(t, mass_unit(a.mass.magic));
+        // The first wavefront ends the tile for all: its lanes add those of the
+        // others, whose multiples and rests are exact sums as they are (in the
+        // place of psi, read to the last row).  Each wavefront for itself: 2048^2
+        // FP16 deviations 45.7 us a step and 45.2 so, FP16 per-node 59.5 and 58.7.
+        static_assert(sizeof ring >= 2 * sizeof(double) * (kMaxTileW - 64), "two sums a lane");
+        double(*const wsum)[2] = reinterpret_cast<double(*)[2]>(&ring[0][0]);
+        double x = msum.sum(a.mass), y = msum.b;
+        if (W > 64) {
+            __syncthreads();
+            if (tid >= 64) {
+                wsum[tid - 64][0] = x;
+                wsum[tid - 64][1] = y;
+            }
+            __syncthreads();
+        }
+        if (tid < 64) {
+            for (int l = tid; l + 64 < W; l += 64) {
+                x += wsum[l][0];
+                y += wsum[l][1];
+            }
+            const MassPart v = mass_wave_part(x, y, mass_unit_inv(a.mass.magic));
+            if (tid == 0) a.partial[tile] = mass_pack(v, mass_unit(a.mass.magic));
         }
     }
 }

@@ -117,3 +117,22 @@ def test_densities_beyond_the_units(L, form, nx, ny):
         hist = d.mass_history()
         say(f"    {hist[-1]!r}, {float(want)!r}")
         assert np.all(np.abs(hist - float(want)) <= nx * ny * 2.0 ** -53 * float(want))
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32_arith32", "f16dev", "f16node"])
+def test_tall_tiles(L, storage):
+    """Tiles of more rows than one lane adds up run as several."""
+    ny, nx = 1300, 300
+    y, x = np.mgrid[:ny, :nx]
+    p = _still(nx, ny, 1.0 + 0.1 * np.cos(0.05 * x) * np.sin(0.01 * y))
+    got = []
+    for w, h in ((64, 3), (64, 511), (128, 512), (256, 513), (256, 1300), (64, 4000)):
+        with L.Domain(p, storage=storage, tile_w=w, tile_h=h, history_capacity=16) as d:
+            L.lbm_set_profiling(d.h, 1)
+            d.step(3)
+            got.append((w, h, d.mass_history()))
+            if storage == "f64":
+                assert _close(d.total_mass(), _sum(d.moments()[0]))
+    say(f"[gpu] masses of tall tiles, {storage}: {got[0][2]}")
+    for w, h, m in got[1:]:
+        assert np.array_equal(m, got[0][2]), (w, h)
