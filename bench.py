@@ -67,9 +67,10 @@ def traffic_record(storage, workload):
 
 def run_gpu(p, storage, steps, warmup, stream, tile_w, tile_h, prof_steps,
             moments=False):
-    """Warm up, then time `steps` steps (captured step graphs, no events);
-    then a separate pass of `prof_steps` steps with HIP events around every
-    launch on the library's stream gives the mean kernel durations."""
+    """Warm up, then time `steps` steps (as the library launches them: captured
+    step graphs, or `blocks` steps per launch; no events); then a separate
+    pass of `prof_steps` single steps, every launch of which records its own
+    start and end, gives the mean kernel durations."""
     import torch
 
     from paper_1908_09235_amd import lbm
@@ -77,6 +78,7 @@ def run_gpu(p, storage, steps, warmup, stream, tile_w, tile_h, prof_steps,
     d = lbm.Domain(p, storage=storage, stream=stream, tile_w=tile_w, tile_h=tile_h,
                    history_capacity=1 << 16)
     info = d.info()
+    blocks = d.blocks()[0]
     d.step(warmup)  # also captures the step graphs the timed run replays
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -98,7 +100,7 @@ def run_gpu(p, storage, steps, warmup, stream, tile_w, tile_h, prof_steps,
         bnd_ms /= max(bnd_n, 1)
     d.close()
     return dict(seconds=t1 - t0, info=info, main_ms=main_ms, bnd_ms=bnd_ms, samples=main_n,
-                drift=drift, mom=mom)
+                drift=drift, mom=mom, blocks=blocks)
 
 
 def copy_bandwidth(torch, mib=1024, reps=20):
@@ -126,8 +128,9 @@ def precision_leg(steps, warmup, stream, prof_steps, check_every, time_steps):
     max-norm relative errors of rho and u over fluid nodes are taken on the
     GPU; a form's steps_within_<tol> is the last checked step up to which
     every check stayed within tol (null if none failed within the run).
-    Rate: each form then times time_steps further steps, and a separate
-    pass of prof_steps gives its mean main-kernel duration."""
+    Rate: each form then times time_steps further steps (steps_per_launch of
+    them a launch on blocks, 0: single steps), and a separate pass of
+    prof_steps single steps gives its mean main-kernel duration."""
     import numpy as np
     import torch
 
@@ -179,6 +182,7 @@ def precision_leg(steps, warmup, stream, prof_steps, check_every, time_steps):
     for st in forms:
         d = doms[st]
         drift = abs(d.total_mass() - m0[st]) / m0[st]
+        blocks = d.blocks()[0]
         d.step(warmup)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
@@ -193,6 +197,7 @@ def precision_leg(steps, warmup, stream, prof_steps, check_every, time_steps):
             lbm.lbm_set_profiling(d.h, 0)
             main_ms = mm / max(mn, 1)
         rec = {"arith": ARITH[st], "mlups": round(fluid * time_steps / sec / 1e6, 1),
+               "steps_per_launch": blocks,
                "main_kernel_ms": round(main_ms, 5),
                "main_kernel_gbs": (round((18 * BYTES_PER_POP[st] + EXTRA_BYTES.get(st, 0)) *
                                          fluid / (main_ms * 1e-3) / 1e9, 1)
@@ -527,30 +532,33 @@ def serve_leg(storage, n_requests, rates, chunk, pool, n_check, gate=1e-5,
 
 
 def two_step_leg(steps, warmup, stream, prof_steps):
-    """Two time steps per pass against one.  Cases: the wall-free shear wave
+    """The two-step kernel (named by its rows per tile) against a domain's
+    default launches: blocks of several steps (steps_per_launch) or single
+    steps.  Cases: the wall-free shear wave
     (2048 x 2048, BGK, no interaction force) in FP32 storage with FP32 and
     with FP64 arithmetic, the benchmark's workload, and the 96 cylinders of
     the precision forms (8192 x 4096) with FP32 arithmetic, in FP32 storage
     and as FP32 deviations.  Per case and
-    setting: the step rate over `steps` timed steps (graph replays), and the
-    mean duration of the main launch over a separate pass of `prof_steps`
-    steps (each launch records its own start and end).  The effective rate
-    counts the algorithmic bytes of the steps one launch advances, 18
-    populations per fluid node per step, against the HBM peak.  `tuned` is
-    the setting lbm_tune_steps_per_pass picks on a fresh domain."""
+    setting: the step rate over `steps` timed steps, and where each launch
+    makes one step or two, its mean duration over a separate pass of
+    `prof_steps` steps (each launch records its own start and end; with
+    blocks, such a pass would time other launches than the run's, and the
+    fields are null).  The effective rate counts the algorithmic bytes of
+    the steps one launch advances, 18 populations per fluid node per step,
+    against the HBM peak, and so does run_gbs over the run's own time.
+    `tuned` is the setting lbm_tune_steps_per_pass picks on a fresh domain."""
     import torch
 
     from lbm_inputs import configs as cfg
     from paper_1908_09235_amd import lbm
 
-    # (name, problem, storage forms, rows per two-step tile: 0 for the
-    # library's default; the droplet's walls run along whole strips, where
-    # shorter tiles pay)
+    # (name, problem, storage forms, rows per two-step tile: the droplet's walls
+    # run along whole strips, where shorter tiles pay)
     cases = [("shear_wave_2048x2048_bgk", lambda: cfg.shear_wave(2048, nx=2048, collision="bgk"),
-              ("f32_arith32", "f32"), 0),
+              ("f32_arith32", "f32"), 16),
              ("droplet_cylinder_2048x2048_mrt_mls_B", cfg.cfg2a, ("f32",), 8),
              ("droplet_cylinder_2048x2048_mrt_mls_B", cfg.cfg2a, ("f32_arith32",), 5),
-             ("cylinders96_8192x4096_bgk_mls_B", cfg.many_cylinders, ("f32_arith32", "f32dev"), 0)]
+             ("cylinders96_8192x4096_bgk_mls_B", cfg.many_cylinders, ("f32_arith32", "f32dev"), 16)]
     out = {}
     for name, make, storages, tile_h in cases:
         p = make()
@@ -562,6 +570,7 @@ def two_step_leg(steps, warmup, stream, prof_steps):
                 if spp == 2:
                     lbm.lbm_set_steps_per_pass(d.h, 2, tile_h)
                     th_used = lbm.lbm_get_steps_per_pass(d.h)[1]
+                blocks = d.blocks()[0]
                 d.step(warmup)  # also captures the step graphs
                 torch.cuda.synchronize()
                 t0 = time.perf_counter()
@@ -569,19 +578,24 @@ def two_step_leg(steps, warmup, stream, prof_steps):
                 torch.cuda.synchronize()
                 sec = time.perf_counter() - t0
                 lbm.lbm_sync(d.h)
-                lbm.lbm_set_profiling(d.h, 1)
-                lbm.lbm_step(d.h, prof_steps)
-                mm, mn, bm, bn = lbm.lbm_kernel_times(d.h)
-                lbm.lbm_set_profiling(d.h, 0)
+                mm = mn = bm = bn = 0
+                if not blocks:
+                    lbm.lbm_set_profiling(d.h, 1)
+                    lbm.lbm_step(d.h, prof_steps)
+                    mm, mn, bm, bn = lbm.lbm_kernel_times(d.h)
+                    lbm.lbm_set_profiling(d.h, 0)
                 d.close()
                 main_ms = mm / max(mn, 1)
-                alg = spp * 18 * BYTES_PER_POP[st] * fluid
+                step_bytes = 18 * BYTES_PER_POP[st] * fluid
+                alg = (blocks or spp) * step_bytes
                 gbs = alg / (main_ms * 1e-3) / 1e9 if main_ms > 0 else None
                 rec[f"steps_per_pass_{spp}"] = {
                     "us_per_step": round(sec / steps * 1e6, 2),
                     "mlups": round(fluid * steps / sec / 1e6, 1),
-                    "main_launch_us": round(main_ms * 1e3, 2),
-                    "boundary_launch_us": round(bm / max(bn, 1) * 1e3, 2),
+                    "steps_per_launch": blocks or spp,
+                    "run_gbs": round(step_bytes * steps / sec / 1e9, 1),
+                    "main_launch_us": round(main_ms * 1e3, 2) if mn else None,
+                    "boundary_launch_us": round(bm / bn * 1e3, 2) if bn else None,
                     "algorithmic_bytes_per_launch": alg,
                     "effective_gbs": gbs and round(gbs, 1),
                     "frac": gbs and round(gbs / PEAK_HBM_GBS, 4)}
@@ -589,7 +603,7 @@ def two_step_leg(steps, warmup, stream, prof_steps):
             # what the library's own tuner picks for this case
             with lbm.Domain(p, storage=st, stream=stream, history_capacity=1 << 12) as d:
                 rec["tuned"] = d.tune_steps_per_pass(max(50, steps // 20))
-            out[f"{name}:{st}" + (f":tile_h{tile_h}" if tile_h else "")] = rec
+            out[f"{name}:{st}:tile_h{tile_h}"] = rec
     return out
 
 
@@ -771,6 +785,7 @@ def main():
             "storage": st, "arith": ARITH[st],
             "mlups": round(fluid * a.other_steps / ro["seconds"] / 1e6, 1),
             "ms_per_step": round(ro["seconds"] / a.other_steps * 1e3, 5),
+            "steps_per_launch": ro["blocks"],  # 0: single steps
             "main_kernel_ms": round(ro["main_ms"], 5),
             "main_kernel_gbs": (round(18 * so * fluid / (ro["main_ms"] * 1e-3) / 1e9, 1)
                                 if ro["main_ms"] > 0 else None),
