@@ -1581,18 +1581,23 @@ size_t Arena::largest_free() const {
 
 namespace {
 
-// Whether a kernel of the domain can store to a caller's array: none, or
-// memory of the domain's own GPU at an address of doubles.  (Other memory --
-// of another GPU, of the host -- is reached by copies.)
-bool stores_reach(const lbm_domain* d, const void* p) {
+// Whether a kernel of the domain can store to a caller's array of n doubles:
+// none, or memory of the domain's own GPU, at an address of doubles, whose
+// allocation goes on for n of them.  (Other memory -- of another GPU, of the
+// host -- is reached by copies, which also refuse an array that ends too soon.)
+bool stores_reach(const lbm_domain* d, const void* p, size_t n) {
     if (!p) return true;
     hipPointerAttribute_t at{};
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice ||
+        at.device != d->device ||
+        hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == d->device &&
-           reinterpret_cast<uintptr_t>(p) % 8 == 0;
+    const uintptr_t at0 = reinterpret_cast<uintptr_t>(p) - reinterpret_cast<uintptr_t>(base);
+    return reinterpret_cast<uintptr_t>(p) % 8 == 0 && at0 <= size && n * 8 <= size - at0;
 }
 
 // Whether two arrays of n doubles share no byte (where they do, copies one
@@ -1634,7 +1639,7 @@ int lbm_moments_device(lbm_domain* d, double* rho, double* ux, double* uy) {
     // Into the caller's arrays by the kernel itself where it can store there;
     // through the domain's planes and three copies otherwise (droplet 2048^2
     // in FP32: 54 us for the kernel, 45 for the copies).
-    if (stores_reach(d, rho) && stores_reach(d, ux) && stores_reach(d, uy) &&
+    if (stores_reach(d, rho, nn) && stores_reach(d, ux, nn) && stores_reach(d, uy, nn) &&
         apart(rho, ux, nn) && apart(rho, uy, nn) && apart(ux, uy, nn)) {
         const void* src = moments_source(d);
         Ctx c = ctx(d);
@@ -1650,12 +1655,13 @@ int lbm_moments_device(lbm_domain* d, double* rho, double* ux, double* uy) {
         if (rc) return rc;
     }
     launch_main(d, moments_source(d), nullptr, true);
-    if (rho && hipMemcpyAsync(rho, d->mom_out, nn * 8, hipMemcpyDeviceToDevice, d->stream))
-        return LBM_EDEVICE;
-    if (ux && hipMemcpyAsync(ux, d->mom_out + nn, nn * 8, hipMemcpyDeviceToDevice, d->stream))
-        return LBM_EDEVICE;
-    if (uy && hipMemcpyAsync(uy, d->mom_out + 2 * nn, nn * 8, hipMemcpyDeviceToDevice, d->stream))
-        return LBM_EDEVICE;
+    double* const outs[3] = {rho, ux, uy};
+    for (int k = 0; k < 3; ++k)
+        if (outs[k] && hipMemcpyAsync(outs[k], d->mom_out + k * nn, nn * 8,
+                                      hipMemcpyDeviceToDevice, d->stream) != hipSuccess) {
+            (void)hipGetLastError();  // (a refused array is no error of the next call)
+            return LBM_EDEVICE;
+        }
     return hipGetLastError() == hipSuccess ? LBM_OK : LBM_EDEVICE;
 }
 
