@@ -387,6 +387,11 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         }
         // ---- pull and psi
         const int mp = reach * (s - 1) + pull, mc = reach * s;
+        constexpr bool SPLIT = sizeof(R) == 8 || DEV != 0;
+        // (read here, so that it travels with the pull: read where the sum begins,
+        // the step waits for it, 100 x 50 in FP64 152.6 us per 64 steps instead of 149.0)
+        MassUnit mass;
+        mass.magic = a.mass.magic;
         S g[NPT][9];
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
@@ -440,9 +445,6 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         __syncthreads();
         // ---- force, moments, collision
         const bool last = s == steps;
-        constexpr bool SPLIT = sizeof(R) == 8 || DEV != 0;
-        MassUnit mass;
-        mass.magic = a.mass.magic;
         MassSum<SPLIT> msum(mass);
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
