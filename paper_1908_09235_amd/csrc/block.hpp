@@ -524,7 +524,7 @@ __device__ __forceinline__ void block_tile(const BlockArgs* args, int cur, int s
         double big = 0.0;
         for (int w = 0; w < NW; ++w) big += mbig[t][w];
         a.partial[(long long)t * a.ntiles + tile] =
-            mass_pack(MassPart{q & 0xffffffffll, q >> 32, fine, big}, mass_unit(a.mass.magic));
+            mass_pack(q, fine, big, mass_unit(a.mass.magic));
     }
 }
 

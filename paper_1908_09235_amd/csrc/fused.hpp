@@ -379,11 +379,11 @@ __global__ __launch_bounds__(kF2Lanes) __attribute__((amdgpu_waves_per_eu(3))) v
     }
 
     const double inv = mass_unit_inv(a.mass.magic), unit = mass_unit(a.mass.magic);
-    const MassPart v1 = mass_wave_part(msum1.sum(a.mass), msum1.b, inv);
-    const MassPart v2 = mass_wave_part(msum2.sum(a.mass), msum2.b, inv);
+    const MassTile v1 = mass_wave_tile(msum1.sum(a.mass), msum1.b, inv, unit);
+    const MassTile v2 = mass_wave_tile(msum2.sum(a.mass), msum2.b, inv, unit);
     if (j == 0) {
-        a.partial1[tile] = mass_pack(v1, unit);
-        a.partial2[tile] = mass_pack(v2, unit);
+        a.partial1[tile] = v1;
+        a.partial2[tile] = v2;
     }
 }
 

@@ -170,21 +170,6 @@ __device__ __forceinline__ double wave_big(double v) {
 __device__ __forceinline__ MassPart mass_wave_sum(const MassPart& p) {
     return MassPart{wave_total(p.lo), wave_total(p.hi), wave_total(p.fine), wave_big(p.big)};
 }
-// A sum of multiples and rests in integers, over the lanes of a wavefront, in
-// lane 0 (at most 2^53 units a lane: 64 of them fit an integer as they are).
-__device__ __forceinline__ MassPart mass_wave_part(double a, double b, double inv) {
-    const double n = a * inv, r = b * inv;
-    // (the rests of 4 kMassRows nodes, a unit each at most: 64 lanes of them hold)
-    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= 4 * kMassRows;
-    // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
-    const double w = rint(n);
-    const long long q = wave_total(in ? (long long)w : 0ll);
-    const long long f =
-        wave_total(in ? (long long)rint(((n - w) + r) * (1.0 / kMassFine)) : 0ll);
-    MassPart v{q & 0xffffffffll, q >> 32, f, wave_big(in ? 0.0 : a + b)};
-    mass_carry(v);
-    return v;
-}
 __device__ __forceinline__ double mass_value(MassPart p, double unit) {
     // three exact doubles, rounded as one sum: the lowest part decides only how
     // the sum of the others rounds
@@ -204,11 +189,25 @@ struct alignas(16) MassTile {
     long long fine;   // integers do not hold.  fine: of 2^-40 units
 };
 // (a workgroup's units fit 63 bits: at most 1024 lanes of 2^53 each)
-__device__ __forceinline__ MassTile mass_pack(MassPart v, double unit) {
-    mass_carry(v);
-    const long long n = v.hi * 4294967296ll + v.lo;
-    if (v.big == 0.0) return MassTile{n, v.fine};
-    return MassTile{__builtin_bit_cast(long long, double(n) * unit + v.big), -1ll};
+__device__ __forceinline__ MassTile mass_pack(long long units, long long fine, double big,
+                                              double unit) {
+    units += fine >> 40;  // (as mass_carry)
+    fine &= 0xffffffffffll;
+    if (big == 0.0) return MassTile{units, fine};
+    return MassTile{__builtin_bit_cast(long long, double(units) * unit + big), -1ll};
+}
+// A sum of multiples and rests over the lanes of a wavefront, in lane 0 (at most
+// 2^53 units a lane: 64 of them fit an integer as they are).
+__device__ __forceinline__ MassTile mass_wave_tile(double a, double b, double inv, double unit) {
+    const double n = a * inv, r = b * inv;
+    // (the rests of 4 kMassRows nodes, a unit each at most: 64 lanes of them hold)
+    const bool in = fabs(n) < 9007199254740992.0 && fabs(r) <= 4 * kMassRows;
+    // (a + b: an FP32 density below a unit's resolution leaves its rest in n)
+    const double w = rint(n);
+    const long long q = wave_total(in ? (long long)w : 0ll);
+    const long long f =
+        wave_total(in ? (long long)rint(((n - w) + r) * (1.0 / kMassFine)) : 0ll);
+    return mass_pack(q, f, wave_big(in ? 0.0 : a + b), unit);
 }
 __device__ __forceinline__ void mass_take(MassPart& v, const MassTile& p) {
     const bool in = p.fine >= 0;
@@ -646,8 +645,9 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
                 x += wsum[l][0];
                 y += wsum[l][1];
             }
-            const MassPart v = mass_wave_part(x, y, mass_unit_inv(a.mass.magic));
-            if (tid == 0) a.partial[tile] = mass_pack(v, mass_unit(a.mass.magic));
+            const MassTile v = mass_wave_tile(x, y, mass_unit_inv(a.mass.magic),
+                                              mass_unit(a.mass.magic));
+            if (tid == 0) a.partial[tile] = v;
         }
     }
 }
@@ -657,23 +657,33 @@ __global__ __launch_bounds__(256) void k_main(MainArgs<S> a, Phys<R> ph) {
     main_tile<S, R, EOS, MOMENTS, DEV, SAVEF>(a, ph, xcd_tile(blockIdx.x, gridDim.x));
 }
 
-// The partials lane `lane` of `lanes` adds up.  (DEPTH is 16, but 8 in k_block,
-// whose registers are counted: with 16, FP32 arithmetic spills 45 of them and
-// 8192 x 4096 takes 451 us a step instead of 418.)
+// The partials that a lane of a wavefront adds up: first + lane, and every
+// `lanes`-th from there.  DEPTH loads are in flight, but four where no more are
+// left: those past the end cost their issue (100 x 50, 91 partials of each of 7 steps:
+// the boundary launch 6.6 us with 16 loads, 5.4 with 4).  (DEPTH is 16, but 8 in
+// k_block, whose registers are counted: with 16, FP32 arithmetic spills 45 of them
+// and 8192 x 4096 takes 451 us a step instead of 418.)
 template <int DEPTH>
 __device__ __forceinline__ MassPart sum_partials(const MassTile* __restrict__ partial, int np,
-                                                 int lane, int lanes) {
+                                                 int first, int lane, int lanes) {
     MassPart v{0, 0, 0, 0.0};
-    // DEPTH loads are issued before their additions (past the end they give 0)
     const rsrc_t rp = make_rsrc(partial, (unsigned)np * (unsigned)sizeof(MassTile));
-    for (int i = lane; i < np; i += DEPTH * lanes) {
-        uint4_t q[DEPTH];
+    // loads are issued before their additions (past the end they give 0; the
+    // scheduler would halve their number for the registers they take)
+    auto take = [&](int i, auto depth) {
+        constexpr int D = decltype(depth)::value;
+        uint4_t q[D];
 #pragma unroll
-        for (int j = 0; j < DEPTH; ++j)
-            q[j] = bload<uint4_t>(rp, (unsigned)(i + j * lanes) * (unsigned)sizeof(MassTile), 0u);
+        for (int j = 0; j < D; ++j)
+            q[j] = bload<uint4_t>(rp, (unsigned)(i + lane + j * lanes) * (unsigned)sizeof(MassTile),
+                                  0u);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < DEPTH; ++j) mass_take(v, __builtin_bit_cast(MassTile, q[j]));
-    }
+        for (int j = 0; j < D; ++j) mass_take(v, __builtin_bit_cast(MassTile, q[j]));
+    };
+    int i = first;
+    for (; i + 4 * lanes < np; i += DEPTH * lanes) take(i, std::integral_constant<int, DEPTH>{});
+    if (i < np) take(i, std::integral_constant<int, 4>{});
     mass_carry(v);
     return v;
 }
@@ -694,7 +704,7 @@ __device__ __forceinline__ void sum_masses(const MassTile* __restrict__ partial,
         const int s = wave / share, part = wave - s * share;
         if (s < cnt) {
             const MassPart v = mass_wave_sum(sum_partials<DEPTH>(partial + (s0 + s) * stride, np,
-                                                                 part * 64 + lane, share * 64));
+                                                                 part * 64, lane, share * 64));
             if (lane == 0) red[wave] = v;
         }
         __syncthreads();

@@ -136,3 +136,23 @@ def test_tall_tiles(L, storage):
     say(f"[gpu] masses of tall tiles, {storage}: {got[0][2]}")
     for w, h, m in got[1:]:
         assert np.array_equal(m, got[0][2]), (w, h)
+
+
+@pytest.mark.parametrize("ntiles", [3, 256, 257, 1024, 1025, 4096, 4097, 5120, 5121, 9217])
+def test_any_number_of_partials(L, ntiles):
+    """256 lanes sum the tiles' parts, 16 at a time and the last four: the edges
+    of both."""
+    nx = 62  # one strip of 64 columns, one row a tile
+    y, x = np.mgrid[:ntiles, :nx]
+    p = _still(nx, ntiles, 1.0 + 0.3 * np.cos(0.7 * x) * np.sin(0.9 * y))
+    with L.Domain(p, storage="f64", tile_w=64, tile_h=1, history_capacity=16) as d:
+        L.lbm_set_profiling(d.h, 1)
+        d.step(2)
+        want = _sum(d.moments()[0])
+        say(f"[gpu] mass from {ntiles} parts: off by {float(Fraction(d.total_mass()) - want)!r}")
+        assert _close(d.total_mass(), want)
+        hist = d.mass_history()
+    with L.Domain(p, storage="f64", tile_w=256, tile_h=16, history_capacity=16) as d:
+        L.lbm_set_profiling(d.h, 1)
+        d.step(2)
+        assert np.array_equal(d.mass_history(), hist)
