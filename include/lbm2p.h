@@ -213,8 +213,10 @@ int lbm_moments_device_noalloc(lbm_domain *d, double *rho, double *ux, double *u
 
 /* Total mass M(t) = sum over fluid nodes of sum_a f*_a (FP64, summed in a
  * way that no order rounds, so equal states give equal bits whatever the
- * launch shape): the m of Sec. 3.2, whose ratio m/m0 the paper plots in
- * Figs. 4-8.  The post-collision
+ * launch shape; the last bits may differ where a density is below 2^-28 of the
+ * largest initial one or more than 2^19 / (rows of a tile x its columns) times
+ * as large, 227 times in the largest default tiles): the m of Sec. 3.2, whose
+ * ratio m/m0 the paper plots in Figs. 4-8.  The post-collision
  * populations carry the same mass as the pre-collision ones. */
 int lbm_total_mass(lbm_domain *d, double *out);
 
@@ -393,7 +395,9 @@ int lbm_batch_remove(lbm_batch *b, int32_t slot);
  * fastest and reports it in out: tile_w, tile_h, persistent, microseconds
  * per step, ring rows.  The steps count as steps of the instances; results
  * do not depend on the configuration.  A batch with no instances keeps its
- * configuration and reports 0 microseconds. */
+ * configuration and reports 0 microseconds.  The time is that of single
+ * steps: runs that go through launches of several (lbm_batch_get_blocks) take
+ * less, and of the configuration only their last step depends on it. */
 int lbm_batch_tune(lbm_batch *b, int64_t steps_per_trial, int32_t out[5]);
 
 /* [0] instances, [1] main-pass tiles, [2] link blocks, [3] arena bytes,

@@ -28,9 +28,10 @@
 // launch 3.5.  Large lattices: the wavefronts in flight (FP64 populations of
 // two regions fill a CU's LDS) and the arithmetic of the halos, 1.3 times a
 // single step's with 2 steps per launch; HBM traffic is halved (331 MB read
-// and 275 MB written per 2 steps at 2048^2 in FP64, counted).  At 2048^2: FP64
-// storage 141 -> 92, FP32 with FP64 arithmetic 77 -> 79 (not used there), FP32
-// arithmetic 75 -> 55; single phase, 4 steps, FP64 140 -> 60.
+// and 283 MB written per 2 steps at 2048^2 in FP64, counted).  At 2048^2, us a
+// step before and in blocks: FP64 storage 132 and 89, FP32 with FP64 arithmetic
+// 77 and 79 (not used there), FP32 arithmetic 72 and 51; single phase, 4 steps,
+// FP64 137 and 51, FP32 arithmetic 73 and 32.
 //
 // Why 32 x 32: the largest square region of which two fit a CU's 160 KB in
 // FP64 (8 x 8 bytes of moving populations and 8 of psi a node; the rest
