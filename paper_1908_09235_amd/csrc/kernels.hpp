@@ -104,11 +104,17 @@ __host__ __device__ constexpr int seg_count(int ny, int tile_h) {
 // What one lane adds up.  SPLIT: as above.  The sum starts at 1.5 * 2^52 units, so
 // that adding a density leaves whole units in it, and what the addition rounded
 // off is the rest (the sum is the larger of the two, so the difference is exact).
-// An FP32 density is a multiple of the unit as it is (down to 2^-16 of the
-// largest).  Splitting the density before adding it took an operation more and
-// two registers: 3000 x 2000 FP16 per-node 86.3 us a step and 85.1 so, the two-step
-// kernel at 2048^2 in FP32 157.5 us a launch and 155.9, FP16 deviations 8192 x 4096
-// 627 and 619.
+// Splitting the density before adding it took an operation more and two
+// registers: 3000 x 2000 FP16 per-node 86.3 us a step and 85.1 so, FP16 deviations
+// 8192 x 4096 in passes of two steps 627 us a launch and 619.
+//   Densities that are sums of FP32 populations (or FP32 themselves) need no split:
+// a lane's sum holds them exactly as it is, down to populations of 2^-26 of the largest
+// density in the default tiles (2^-19 in the tallest), and its rest over whole
+// units comes off where the tile ends.  So the main pass adds them as they are (FP32
+// with FP64 arithmetic, us a step with splits and without: 1024^2 23.97 and 23.76,
+// 1190^2 30.47 and 30.24, 1792^2 51.7 and 51.4, 2048^2 the same).  The two-step kernel
+// keeps the splits with FP64 arithmetic, where its registers fall out worse without
+// (2048^2 by 8 rows 82.5 and 87.1), and so do blocks (no difference).
 template <bool SPLIT>
 struct MassSum {
     double a, b;
@@ -515,7 +521,7 @@ __device__ __forceinline__ void main_tile(const MainArgs<S>& a, const Phys<R>& p
         ring[slot][tid] = (L.fl & FL_SOLID) ? pw : psi_of<EOS, R>(rho, ph);
     };
 
-    MassSum<sizeof(R) == 8 || DEV != 0> msum(a.mass);
+    MassSum<sizeof(S) == 8 || DEV != 0> msum(a.mass);
     // row k: collide with psi of rows k-1, k, k+1; then prefetch row k+3
     auto step = [&](int k, RowLoad<S, R, NR>& Lc, RowLoad<S, R, NR>& Ln) {
         const int y = row_of(k);

@@ -156,3 +156,28 @@ def test_any_number_of_partials(L, ntiles):
         L.lbm_set_profiling(d.h, 1)
         d.step(2)
         assert np.array_equal(d.mass_history(), hist)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f32_arith32"])
+@pytest.mark.parametrize("rule,fix", [("mls", "B"), ("ibb_quadratic", "A")])
+def test_fp32_populations(L, storage, rule, fix):
+    """Sums of FP32 populations, which are not split: the same bits from every
+    tile, from two steps per pass and from blocks, and that of the densities."""
+    p = cfg.cfg2a(rule=rule, fix=fix, scale=2.3)
+    got = []
+    for w, h, two in ((256, 9, 0), (64, 3, 0), (128, 37, 0), (256, 512, 0), (0, 0, 0), (0, 0, 8)):
+        if two and rule == "ibb_quadratic":
+            continue  # (refused)
+        with L.Domain(p, storage=storage, tile_w=w, tile_h=h, history_capacity=64) as d:
+            if two:
+                L.lbm_set_steps_per_pass(d.h, 2, two)
+            elif w:
+                L.lbm_set_profiling(d.h, 1)
+            d.step(40)
+            got.append(((w, h, two, d.blocks()[0]), d.mass_history()))
+            if storage == "f32":
+                assert _close(d.total_mass(), _sum(d.moments()[0]))
+    say(f"[gpu] masses of FP32 populations, {storage} {rule}: {got[0][1][-2:]}")
+    assert got[4][0][3] > 0  # blocks among them
+    for k, m in got[1:]:
+        assert np.array_equal(m, got[0][1]), k
