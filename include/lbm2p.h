@@ -214,9 +214,10 @@ int lbm_moments_device_noalloc(lbm_domain *d, double *rho, double *ux, double *u
 /* Total mass M(t) = sum over fluid nodes of sum_a f*_a (FP64, summed in a
  * way that no order rounds, so equal states give equal bits whatever the
  * launch shape; the last bits may differ where a density is below 2^-28 (a
- * population held in FP32: 2^-19) of the largest initial one, or more than 2^19 / (rows of a tile x its columns) times
- * as large, 227 times in the largest default tiles): the m of Sec. 3.2, whose
- * ratio m/m0 the paper plots in Figs. 4-8.  The post-collision
+ * population held in FP32: 2^-19) of the largest initial one, or more than
+ * 2^19 / (rows of a tile x its columns) times as large, 227 times in the
+ * largest default tiles): the m of Sec. 3.2, whose ratio m/m0 the paper plots
+ * in Figs. 4-8.  The post-collision
  * populations carry the same mass as the pre-collision ones. */
 int lbm_total_mass(lbm_domain *d, double *out);
 
